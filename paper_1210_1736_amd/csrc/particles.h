@@ -27,7 +27,8 @@ constexpr int kNDiag = kDiagLost + 1;
 constexpr int kPreVals = kMaxGal * 4;  // per galaxy [m, m x, m y, m z]
 constexpr int kRedBlocks = 1024;       // blocks per instance of the loss-test / COM pass
 constexpr int kForceBlocksMax = 2048;  // blocks per instance of the force pass
-constexpr int kDepChunk = 8192;        // particles per block of the mass assignment
+constexpr int kDepChunkMax = 8192;     // most particles per block of the mass assignment
+constexpr int kDepBlocks = 1024;       // blocks it aims at where smaller chunks give them
 constexpr int kArgParts = 256;         // blocks per galaxy of the densest-cell search
 
 // One grid geometry as the kernels use it (all float64, computed on the host
@@ -147,6 +148,21 @@ struct Span {
 };
 
 int force_blocks(int64_t n);
+
+// Particles per block of the mass assignment of an instance of n: the
+// smallest power of two in 256..8192 that leaves at most kDepBlocks blocks.
+// A block's chunk is a serial chain (about 1.8 us per 256 particles), so few
+// particles are spread over many short chunks; large chunks flush fewer
+// coarse cells.  Chunks of 8192 throughout, against this rule: 59 -> 6.2 us
+// for 20011 particles (FP32, 32^3), 37 -> 6.0 us for 100k (FP64, 64^3),
+// 68 -> 19 us for 1M in two galaxies (FP64 fixed-point, 64^3), 109 -> 37 us
+// for 300k (FP64, 128^3); 8.5M particles keep 8192.  Aiming at 512 or 2048
+// blocks measured the same below 300k particles and 1-3% slower a step at 1M.
+__host__ __device__ inline int dep_chunk(int64_t n) {
+  int c = 256;
+  while (c < kDepChunkMax && (int64_t)c * kDepBlocks < n) c *= 2;
+  return c;
+}
 
 template <typename T>
 sbx_status launch_zero(T* p, size_t n, hipStream_t s);

@@ -370,7 +370,10 @@ int force_blocks(int64_t n) {
 
 static int64_t blocks_particles(const InstInfo& f) { return f.n > 0 ? (f.n + 255) / 256 : 1; }
 static int64_t blocks_force(const InstInfo& f) { return force_blocks(f.n); }
-static int64_t blocks_deposit(const InstInfo& f) { return f.n > 0 ? (f.n + kDepChunk - 1) / kDepChunk : 1; }
+static int64_t blocks_deposit(const InstInfo& f) {
+  const int c = dep_chunk(f.n);
+  return f.n > 0 ? (f.n + c - 1) / c : 1;
+}
 static int64_t blocks_red(const InstInfo&) { return kRedBlocks; }
 static int64_t blocks_dm(const InstInfo& f) {
   const int64_t b = (int64_t)((f.dm_elems + 1023) / 1024);
@@ -806,7 +809,8 @@ __global__ void __launch_bounds__(256)
     else return glb(cell);
   };
   __syncthreads();
-  const int64_t base = (int64_t)lb * kDepChunk;
+  const int chunk = dep_chunk(I.n), rounds = chunk / 256;
+  const int64_t base = (int64_t)lb * chunk;
   // The next particle is loaded one iteration ahead, every field whatever
   // its flag, so that the loads go out together and the flag is waited for
   // only where it is used (l = 1 marks no particle).
@@ -825,11 +829,11 @@ __global__ void __launch_bounds__(256)
   int gn = 0;
   T xn = (T)0, yn = (T)0, zn = (T)0, mn = (T)0;
   fetch(base + threadIdx.x, lnx, gn, xn, yn, zn, mn);
-  for (int j = 0; j < kDepChunk / 256; ++j) {
+  for (int j = 0; j < rounds; ++j) {
     const bool ok = lnx == 0;
     const int g = gn;
     const T xs = xn, ys = yn, zs = zn, ms = mn;
-    if (j + 1 < kDepChunk / 256) fetch(base + (j + 1) * 256 + threadIdx.x, lnx, gn, xn, yn, zn, mn);
+    if (j + 1 < rounds) fetch(base + (j + 1) * 256 + threadIdx.x, lnx, gn, xn, yn, zn, mn);
     // fine: key on the finest level, or kNoKey; coarse keys c1, c2 go
     // through the table
     uint32_t fine = kNoKey, c1 = kNoKey, c2 = kNoKey;
