@@ -252,17 +252,9 @@ void free_particles(sbx_ctx* c) {
     c->set[0] = PSet();
     c->bound = false;
   }
-  for (int s = 0; s < 2; ++s) {
-    PSet& q = c->set[s];
-    for (int k = 0; k < 3; ++k) {
-      free_ptr(q.x[k]);
-      free_ptr(q.v[k]);
-    }
-    free_ptr(q.m);
-    free_typed(q.comp);
-    free_typed(q.gal);
-    free_typed(q.lost);
-    free_typed(q.id);
+  for (PSet& q : c->set) {
+    free_ptr(q.block);
+    q = PSet();
   }
   free_typed(c->key);
   free_typed(c->rank);
@@ -824,6 +816,36 @@ bool on_device(const void* p, int device) {
   return (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged) && at.device == device;
 }
 
+// One allocation for a particle set; a read-back also uses the spare set's
+// as n records of eight values (launch_state_out).
+static sbx_status alloc_set(PSet& q, int64_t n, size_t es) {
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) & ~(size_t)255;
+    return o;
+  };
+  size_t xo[3], vo[3];
+  for (int k = 0; k < 3; ++k) {
+    xo[k] = take(es * n);
+    vo[k] = take(es * n);
+  }
+  const size_t mo = take(es * n), ido = take(sizeof(int32_t) * n);
+  const size_t co = take(n), go = take(n), lo = take(n);
+  SBX_TRY(dev_alloc(&q.block, std::max(at, 8 * es * (size_t)n)));
+  char* b = (char*)q.block;
+  for (int k = 0; k < 3; ++k) {
+    q.x[k] = b + xo[k];
+    q.v[k] = b + vo[k];
+  }
+  q.m = b + mo;
+  q.id = (int32_t*)(b + ido);
+  q.comp = (int8_t*)(b + co);
+  q.gal = (int8_t*)(b + go);
+  q.lost = (uint8_t*)(b + lo);
+  return SBX_OK;
+}
+
 sbx_status load_impl(sbx_ctx* c, int64_t n, const double* x, const double* v, const double* m,
                      const int8_t* comp, const int8_t* gal, bool dev) {
   if (!c || n <= 0 || !x || !v || !m || !comp || !gal) {
@@ -888,19 +910,7 @@ sbx_status load_impl(sbx_ctx* c, int64_t n, const double* x, const double* v, co
   }
   SBX_HIP(hipStreamSynchronize(c->stream));
   free_particles(c);
-  const size_t es = c->esz;
-  for (int s = 0; s < 2; ++s) {
-    PSet& q = c->set[s];
-    for (int k = 0; k < 3; ++k) {
-      SBX_TRY(dev_alloc(&q.x[k], es * n));
-      SBX_TRY(dev_alloc(&q.v[k], es * n));
-    }
-    SBX_TRY(dev_alloc(&q.m, es * n));
-    SBX_TRY(dev_alloc((void**)&q.comp, n));
-    SBX_TRY(dev_alloc((void**)&q.gal, n));
-    SBX_TRY(dev_alloc((void**)&q.lost, n));
-    SBX_TRY(dev_alloc((void**)&q.id, sizeof(int32_t) * n));
-  }
+  for (PSet& q : c->set) SBX_TRY(alloc_set(q, n, c->esz));
   SBX_TRY(dev_alloc((void**)&c->key, sizeof(uint32_t) * n));
   SBX_TRY(dev_alloc((void**)&c->rank, sizeof(uint32_t) * n));
   c->n = n;
@@ -975,26 +985,26 @@ sbx_status get_impl(sbx_ctx* c, double* x, double* v, uint8_t* lost, bool dev) {
         return SBX_EINVAL;
       }
   const PSet& q = c->set[c->cur];
+  auto out = [&](double* xo, double* vo, uint8_t* lo) -> sbx_status {
+    void* rec = c->bound ? nullptr : c->set[c->cur ^ 1].block;
+    if (c->cfg.prec == SBX_FP64)
+      return launch_state_out<double>(pset_dev<double>(q, c->n), (double*)rec, xo, vo, lo, c->stream);
+    return launch_state_out<float>(pset_dev<float>(q, c->n), (float*)rec, xo, vo, lo, c->stream);
+  };
+  if (dev) {
+    SBX_TRY(out(x, v, lost));
+    SBX_HIP(hipStreamSynchronize(c->stream));
+    return SBX_OK;
+  }
   double* stage = nullptr;
-  SBX_TRY(dev_alloc((void**)&stage, sizeof(double) * 6 * c->n));
-  double* stage2 = stage + 3 * c->n;
+  SBX_TRY(dev_alloc((void**)&stage, sizeof(double) * 6 * c->n + c->n));
+  double* sv = stage + 3 * c->n;
+  uint8_t* sl = (uint8_t*)(stage + 6 * c->n);
   auto run = [&]() -> sbx_status {
-    for (int which = 0; which < 2; ++which) {
-      double* out = which == 0 ? x : v;
-      void* const* src = which == 0 ? q.x : q.v;
-      if (!out) continue;
-      if (c->cfg.prec == SBX_FP64)
-        SBX_TRY(launch_join3<double>((double*)src[0], (double*)src[1], (double*)src[2], stage, c->n, c->stream));
-      else
-        SBX_TRY(launch_join3<float>((float*)src[0], (float*)src[1], (float*)src[2], stage, c->n, c->stream));
-      SBX_TRY(launch_unpermute<double>(stage, q.id, dev ? out : stage2, c->n, 3, c->stream));
-      if (!dev) SBX_HIP(hipMemcpyAsync(out, stage2, sizeof(double) * 3 * c->n, hipMemcpyDeviceToHost, c->stream));
-      SBX_HIP(hipStreamSynchronize(c->stream));
-    }
-    if (lost) {
-      SBX_TRY(launch_unpermute<uint8_t>(q.lost, q.id, dev ? lost : (uint8_t*)stage, c->n, 1, c->stream));
-      if (!dev) SBX_HIP(hipMemcpyAsync(lost, stage, c->n, hipMemcpyDeviceToHost, c->stream));
-    }
+    SBX_TRY(out(x ? stage : nullptr, v ? sv : nullptr, lost ? sl : nullptr));
+    if (x) SBX_HIP(hipMemcpyAsync(x, stage, sizeof(double) * 3 * c->n, hipMemcpyDeviceToHost, c->stream));
+    if (v) SBX_HIP(hipMemcpyAsync(v, sv, sizeof(double) * 3 * c->n, hipMemcpyDeviceToHost, c->stream));
+    if (lost) SBX_HIP(hipMemcpyAsync(lost, sl, c->n, hipMemcpyDeviceToHost, c->stream));
     SBX_HIP(hipStreamSynchronize(c->stream));
     return SBX_OK;
   };

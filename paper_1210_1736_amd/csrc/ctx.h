@@ -23,8 +23,10 @@ struct Green {
   double rel_imag;
 };
 
-// One set of particle arrays (device, context precision).
+// One set of particle arrays (device, context precision), carved from one
+// allocation of at least particle_block_bytes (null: borrowed storage).
 struct PSet {
+  void* block = nullptr;
   void* x[3] = {};
   void* v[3] = {};
   void* m = nullptr;

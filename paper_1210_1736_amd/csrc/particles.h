@@ -260,8 +260,12 @@ sbx_status launch_convert_out(const T* src, double* dst, size_t n, hipStream_t s
 // split host n*3 row-major doubles (already on device) into 3 SoA arrays of T
 template <typename T>
 sbx_status launch_split3(const double* src, T* x0, T* x1, T* x2, int64_t n, hipStream_t s);
+
+// Positions, velocities (n*3 row-major float64) and lost flags of a set in
+// the caller's order (x[3 id[i]] and so on); any output may be null.  rec:
+// n records of eight values to stage them in, or null (see the kernels).
 template <typename T>
-sbx_status launch_join3(const T* x0, const T* x1, const T* x2, double* dst, int64_t n,
-                        hipStream_t s);
+sbx_status launch_state_out(const PartDev<T>& p, T* rec, double* x, double* v, uint8_t* lost,
+                            hipStream_t s);
 
 }  // namespace sbx

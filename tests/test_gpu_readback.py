@@ -1,0 +1,46 @@
+"""Device and host read-back of a reordered context in the caller's order, on
+both sides of the particle counts where the staged form takes over (2^19 in
+FP32, 3 * 2^20 in FP64) and with outputs left out.  The particles have not
+moved (a step of no length, lost ones off the grid), so every value is exact:
+bit equality."""
+import numpy as np
+import pytest
+
+from tests import common as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sbx():
+    from paper_1210_1736_amd import sbx as m
+    return m
+
+
+@pytest.mark.parametrize("prec,n", [(0, 1), (0, 259), (0, 2 ** 19 - 1), (0, 2 ** 19), (0, 2 ** 19 + 77),
+                                    (1, 1), (1, 2 ** 19), (1, 3 * 2 ** 20 - 1), (1, 3 * 2 ** 20 + 5)])
+def test_readback_in_callers_order(sbx, prec, n):
+    import torch
+    rng = np.random.default_rng(np.random.SeedSequence([1210, 1736, 981, n]))
+    x = T.rounded(rng.uniform(-1.05, 1.05, (n, 3)), prec)  # grid of half-extent 1: some are lost
+    v = T.rounded(rng.normal(size=(n, 3)), prec)
+    ctx = sbx.Context(prec=prec)
+    ctx.sbx_build_grids([sbx.make_hierarchy([(16, 1.0, 1.0)])])
+    ctx.sbx_load_particles(x, v, np.full(n, 1.0 / n), np.zeros(n, np.int8), np.zeros(n, np.int8))
+    ctx.sbx_step(0.0, 1)
+    xh, vh, lh = ctx.sbx_get_particles()
+    assert np.array_equal(xh, x) and np.array_equal(vh, v)
+    cell = np.floor(x * 6.0 + 8.0 + 0.5)   # gamma = (16 - 4) / 2
+    assert np.array_equal(lh, ((cell < 2) | (cell > 13)).any(axis=1))
+    new = lambda *s: torch.full(s, -7.0, dtype=torch.float64, device="cuda")
+    for wx, wv, wl in ((1, 1, 1), (1, 0, 0), (0, 1, 1), (0, 0, 1)):
+        xd, vd = new(n, 3), new(n, 3)
+        ld = torch.full((n,), 9, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        ctx.sbx_get_particles_device(xd.data_ptr() if wx else None, vd.data_ptr() if wv else None,
+                                     ld.data_ptr() if wl else None)
+        same = lambda t, a, w, blank: bool(np.array_equal(t.cpu().numpy(), a) if w else (t == blank).all())
+        assert same(xd, xh, wx, -7.0) and same(vd, vh, wv, -7.0) and same(ld, lh.astype(np.uint8), wl, 9)
+    ctx.sbx_step(0.0, 1)  # the staging left the live set alone
+    assert np.array_equal(ctx.sbx_get_particles()[0], x)
+    ctx.close()
