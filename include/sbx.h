@@ -166,9 +166,9 @@ sbx_status sbx_load_particles_device(sbx_ctx* ctx, int64_t n, const double* x, c
  * the context stream; getters copy from them.  The storage is borrowed until
  * sbx_destroy or the next sbx_load_particles*, sbx_bind_device_particles or
  * sbx_load: the caller keeps it alive and orders its own work on it with the
- * context stream.  Bound particles are never reordered (the cell sort, a
- * performance setting only, is skipped), and a context holding them cannot
- * join a batch.  Validated on the device as sbx_load_particles_device
+ * context stream.  Bound particles are never reordered (steps skip the cell
+ * sort, a performance setting only; a differentiable segment runs on a sorted
+ * copy of its own), and a context holding them cannot join a batch.  Validated on the device as sbx_load_particles_device
  * (SBX_EINVAL); x, v and lost must not overlap any other array (SBX_EINVAL).
  * Lost flags are taken as given. */
 sbx_status sbx_bind_device_particles(sbx_ctx* ctx, int64_t n, void* x, void* v, void* m,

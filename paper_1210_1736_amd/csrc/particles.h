@@ -211,22 +211,32 @@ template <typename T>
 sbx_status launch_indices(const InstDev<T>* inst, const int* cur, int64_t n, int galaxy, int level,
                           int32_t* idx, int8_t* cls, hipStream_t s);
 
+// What the reverse of one cycle reads of it: positions before the cycle, the
+// flags of the particles that sat it out, and how far (in elements) the kept
+// fields lie from the instance's grid block.
+template <typename T>
+struct AdjCycle {
+  const T* x[3];
+  const uint8_t* out;
+  ptrdiff_t fields;
+};
+
 // Reverse mode of a leapfrog segment (single instance, fixed centres).
 // init: loss (one double) and seeds of the adjoints; step: one reverse cycle
-// at the positions in the live set with the forward fields in the grids,
-// adjoint sources scattered into B; gather: mass gradient from the adjoint
-// potentials P.  `out` marks the particles that sat out the cycle (lost at
-// its start): their adjoints pass through unchanged and they gather nothing.
+// at its positions and forward fields, adjoint sources scattered into B;
+// gather: mass gradient from the adjoint potentials P.  Particles that sat
+// out the cycle (lost at its start) pass their adjoints through unchanged
+// and gather nothing.
 template <typename T>
 sbx_status launch_adj_init(const InstDev<T>* inst, const int* cur, int64_t n, int sel_comp,
                            int sel_gal, double* lx, double* lv, double* gm, double* partial,
                            double* loss, hipStream_t s);
 template <typename T>
-sbx_status launch_adj_step(const InstDev<T>* inst, const int* cur, int64_t n, const GridsDev<T>& B,
-                           const uint8_t* out, double* lx, double* lv, hipStream_t s);
+sbx_status launch_adj_step(const InstDev<T>* inst, int64_t n, const AdjCycle<T>& at,
+                           const GridsDev<T>& B, double* lx, double* lv, hipStream_t s);
 template <typename T>
-sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, const GridsDev<T>& P,
-                             const uint8_t* out, double* gm, hipStream_t s);
+sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, const AdjCycle<T>& at,
+                             const GridsDev<T>& P, double* gm, hipStream_t s);
 
 sbx_status launch_iota(int32_t* id, int64_t n, hipStream_t s);
 
@@ -267,5 +277,8 @@ sbx_status launch_split3(const double* src, T* x0, T* x1, T* x2, int64_t n, hipS
 template <typename T>
 sbx_status launch_state_out(const PartDev<T>& p, T* rec, double* x, double* v, uint8_t* lost,
                             hipStream_t s);
+// Positions, velocities and lost flags of p back to its order's home set.
+template <typename T>
+sbx_status launch_state_home(const PartDev<T>& p, const PartDev<T>& home, hipStream_t s);
 
 }  // namespace sbx

@@ -1421,8 +1421,8 @@ __global__ void __launch_bounds__(256)
 
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_adj_step(const InstDev<T>* __restrict__ inst, const int* __restrict__ cur, GridsDev<T> Bg,
-               const uint8_t* __restrict__ out, double* __restrict__ lx, double* __restrict__ lv) {
+    k_adj_step(const InstDev<T>* __restrict__ inst, AdjCycle<T> at, GridsDev<T> Bg, double* __restrict__ lx,
+               double* __restrict__ lv) {
   __shared__ uint32_t tkey[kAdjTable];
   __shared__ T tval[kAdjTable];
   __shared__ double cen[3 * kMaxGal];  // read from LDS inside the galaxy loop
@@ -1443,13 +1443,12 @@ __global__ void __launch_bounds__(256)
   }
   __syncthreads();
   const AdjSink<T> sink{tkey, tval, &Bs};
-  const PartDev<T> p = I.p[cur[0]];
   const SysDev& sys = I.sys;
   const double dt = I.dt;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   // Every lane takes part in the wavefront sums below, with or without a
   // particle (act); a lane without one carries no key.
-  const bool act = i < p.n && !out[i];
+  const bool act = i < I.n && !at.out[i];
   double l[3] = {0.0, 0.0, 0.0}, mu[3] = {0.0, 0.0, 0.0};
   double x = 0.0, y = 0.0, z = 0.0;
   if (act) {
@@ -1463,9 +1462,9 @@ __global__ void __launch_bounds__(256)
     mu[0] = dt * w0;
     mu[1] = dt * w1;
     mu[2] = dt * w2;
-    x = (double)p.x[0][i];
-    y = (double)p.x[1][i];
-    z = (double)p.x[2][i];
+    x = (double)at.x[0][i];
+    y = (double)at.x[1][i];
+    z = (double)at.x[2][i];
   }
   const GridsDev<T>& F = I.G;
   for (int g = 0; g < sys.ngal; ++g) {
@@ -1499,7 +1498,7 @@ __global__ void __launch_bounds__(256)
       uint32_t key = kNoKey;
       if (slot >= 0) {
         key = dep_key(g, slot, L, cl.idx[lev]);
-        eq8_adjoint_weights(F.g[g][slot], L, cl.idx[lev], outer ? ox : dx, outer ? oy : dy,
+        eq8_adjoint_weights(F.g[g][slot] + at.fields, L, cl.idx[lev], outer ? ox : dx, outer ? oy : dy,
                             outer ? oz : dz, sys.taylor, mu, l, w);
       } else {
 #pragma unroll
@@ -1559,26 +1558,26 @@ __device__ __forceinline__ const T* cell_ptr(const T* grid, const LevelDev& L, c
 // read at its source cell (the transpose of the nearest-grid-point deposit).
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_adj_gather(const InstDev<T>* __restrict__ inst, const int* __restrict__ cur, GridsDev<T> Pg,
-                 const uint8_t* __restrict__ out, double* __restrict__ gm) {
+    k_adj_gather(const InstDev<T>* __restrict__ inst, const int* __restrict__ cur, AdjCycle<T> at,
+                 GridsDev<T> Pg, double* __restrict__ gm) {
   const InstDev<T>& I = inst[0];
   const PartDev<T> p = I.p[cur[0]];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= p.n || out[i]) return;
+  if (i >= p.n || at.out[i]) return;
   const int g = p.gal[i];
   const HierDev& h = I.sys.h[g];
   Classified c;
-  classify(h, I.centres + 3 * g, (double)p.x[0][i], (double)p.x[1][i], (double)p.x[2][i], c);
+  classify(h, I.centres + 3 * g, (double)at.x[0][i], (double)at.x[1][i], (double)at.x[2][i], c);
   double s = 0.0;
-  auto at = [&](int slot, int lev) { return (double)*cell_ptr(Pg.g[g][slot], h.lv[lev], c.idx[lev]); };
+  auto psi = [&](int slot, int lev) { return (double)*cell_ptr(Pg.g[g][slot], h.lv[lev], c.idx[lev]); };
   if (h.n_levels == 1) {
-    if (c.cls == SBX_OUTER) s = at(0, 0);
+    if (c.cls == SBX_OUTER) s = psi(0, 0);
   } else if (c.cls == SBX_CORE) {
-    s = at(0, 0) + at(2, 1) + at(4, 2);
+    s = psi(0, 0) + psi(2, 1) + psi(4, 2);
   } else if (c.cls == SBX_RING) {
-    s = at(1, 1) + at(2, 1) + at(4, 2);
+    s = psi(1, 1) + psi(2, 1) + psi(4, 2);
   } else if (c.cls == SBX_OUTER) {
-    s = at(3, 2) + at(4, 2);
+    s = psi(3, 2) + psi(4, 2);
   }
   gm[i] += s;
 }
@@ -1689,6 +1688,19 @@ __global__ void __launch_bounds__(256)
     if (v)
       for (int k = 0; k < 3; ++k) glb(v)[3 * j + k] = (double)glb((const T*)p.v[k])[i];
     if (lost) glb(lost)[j] = glb((const uint8_t*)p.lost)[i];
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_state_home(PartDev<T> p, PartDev<T> home) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * 256) {
+    const int64_t j = glb((const int32_t*)p.id)[i];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      glb(home.x[k])[j] = glb((const T*)p.x[k])[i];
+      glb(home.v[k])[j] = glb((const T*)p.v[k])[i];
+    }
+    glb(home.lost)[j] = glb((const uint8_t*)p.lost)[i];
   }
 }
 
@@ -1853,21 +1865,20 @@ sbx_status launch_adj_init(const InstDev<T>* inst, const int* cur, int64_t n, in
 }
 
 template <typename T>
-sbx_status launch_adj_step(const InstDev<T>* inst, const int* cur, int64_t n, const GridsDev<T>& B,
-                           const uint8_t* out, double* lx, double* lv, hipStream_t s) {
+sbx_status launch_adj_step(const InstDev<T>* inst, int64_t n, const AdjCycle<T>& at,
+                           const GridsDev<T>& B, double* lx, double* lv, hipStream_t s) {
   if (n == 0) return SBX_OK;
-  hipLaunchKernelGGL((k_adj_step<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, inst, cur, B,
-                     out, lx, lv);
+  hipLaunchKernelGGL((k_adj_step<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, inst, at, B, lx, lv);
   SBX_HIP(hipGetLastError());
   return SBX_OK;
 }
 
 template <typename T>
-sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, const GridsDev<T>& P,
-                             const uint8_t* out, double* gm, hipStream_t s) {
+sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, const AdjCycle<T>& at,
+                             const GridsDev<T>& P, double* gm, hipStream_t s) {
   if (n == 0) return SBX_OK;
-  hipLaunchKernelGGL((k_adj_gather<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, inst, cur, P,
-                     out, gm);
+  hipLaunchKernelGGL((k_adj_gather<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, inst, cur, at, P,
+                     gm);
   SBX_HIP(hipGetLastError());
   return SBX_OK;
 }
@@ -1998,6 +2009,14 @@ sbx_status launch_state_out(const PartDev<T>& p, T* rec, double* x, double* v, u
   return SBX_OK;
 }
 
+template <typename T>
+sbx_status launch_state_home(const PartDev<T>& p, const PartDev<T>& home, hipStream_t s) {
+  const unsigned g = (unsigned)std::min<int64_t>((p.n + 255) / 256, 8192);
+  hipLaunchKernelGGL((k_state_home<T>), dim3(g), dim3(256), 0, s, p, home);
+  SBX_HIP(hipGetLastError());
+  return SBX_OK;
+}
+
 #define SBX_INST(T)                                                                              \
   template sbx_status launch_zero<T>(T*, size_t, hipStream_t);                                   \
   template sbx_status launch_zero_grids<T>(const InstDev<T>*, const std::vector<InstInfo>&,      \
@@ -2017,15 +2036,15 @@ sbx_status launch_state_out(const PartDev<T>& p, T* rec, double* x, double* v, u
   template sbx_status launch_adj_init<T>(const InstDev<T>*, const int*, int64_t, int, int,       \
                                          double*, double*, double*, double*, double*,            \
                                          hipStream_t);                                           \
-  template sbx_status launch_adj_step<T>(const InstDev<T>*, const int*, int64_t,                 \
-                                         const GridsDev<T>&, const uint8_t*, double*, double*,   \
-                                         hipStream_t);                                           \
+  template sbx_status launch_adj_step<T>(const InstDev<T>*, int64_t, const AdjCycle<T>&,         \
+                                         const GridsDev<T>&, double*, double*, hipStream_t);     \
   template sbx_status launch_adj_gather<T>(const InstDev<T>*, const int*, int64_t,               \
-                                           const GridsDev<T>&, const uint8_t*, double*,          \
+                                           const AdjCycle<T>&, const GridsDev<T>&, double*,      \
                                            hipStream_t);                                         \
   template sbx_status launch_convert_in<T>(const double*, T*, size_t, hipStream_t);              \
   template sbx_status launch_convert_out<T>(const T*, double*, size_t, hipStream_t);             \
   template sbx_status launch_split3<T>(const double*, T*, T*, T*, int64_t, hipStream_t);         \
+  template sbx_status launch_state_home<T>(const PartDev<T>&, const PartDev<T>&, hipStream_t);   \
   template sbx_status launch_state_out<T>(const PartDev<T>&, T*, double*, double*, uint8_t*,     \
                                           hipStream_t);
 SBX_INST(float)
