@@ -1,10 +1,11 @@
 // Disc diagnostics of the paper's analysis (Sec. 4.2 and 5.2-5.4): heat of
 // the disc with the mean circular velocity from radial bins of equal
 // particle numbers, RMS thickness per bin, vertical density profile and
-// velocity dispersions in an annulus.  The radial order comes from a stable
-// least-significant-digit radix sort of the FP64 radii (ties keep the
-// caller's particle order).  Every sum except the vertical profile is
-// reduced in a fixed order.
+// velocity dispersions in an annulus.  The radial order is by FP64 radius,
+// ties in the caller's particle order.  Every sum except the vertical profile
+// is reduced in a fixed order.
+#include <type_traits>
+
 #include "ctx.h"
 
 using namespace sbx;
@@ -16,36 +17,126 @@ constexpr int kRsChunks = kRsTile / 64;
 constexpr int kMaxBins = 2048;
 constexpr int kMaxZ = 1024;
 constexpr int kAnBlocks = 512;  // blocks of the heat / annulus pass
+constexpr int kBulkBlocks = 1024;
 // per-block partial row: heat, annulus count, sum vR, vR^2, vphi, vphi^2, vz, vz^2
 constexpr int kAnVals = 8;
 
 // ------------------------------------------------------------- selection --
-// flag (caller order) of the disc particles
+// The disc particles are numbered in the caller's order (k = 0, 1, ...): a bit
+// per particle, set at its caller's index, the popcounts of the words scanned.
+// Bits instead of a word per particle keep the scattered writes of the 8.5M
+// galaxy in 1 MB (169 -> 84 us).
 template <typename T>
-__global__ void k_disc_flags(PartDev<T> p, int comp, int gal, uint32_t* __restrict__ flag) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    flag[p.id[i]] = (p.comp[i] == comp && p.gal[i] == gal && !p.lost[i]) ? 1u : 0u;
+__global__ void __launch_bounds__(256)
+    k_disc_mask(PartDev<T> p, int comp, int gal, uint32_t* __restrict__ mask) {
+  const int lane = threadIdx.x & 63;
+  const int64_t rounds = (p.n + 63) / 64;
+  for (int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6; w < rounds; w += (int64_t)gridDim.x * 4) {
+    const int64_t i = w * 64 + lane;
+    const bool in = i < p.n;
+    const int32_t id = in ? p.id[i] : 0;
+    const bool sel = in && p.comp[i] == comp && p.gal[i] == gal && !p.lost[i];
+    const uint64_t bits = __ballot(sel);
+    const int32_t id0 = __builtin_amdgcn_readfirstlane(id);
+    if (__ballot(in && id != id0 + lane) == 0ull && (id0 & 63) == 0) {
+      // the caller's own order: this wavefront owns its words
+      if (in && (lane & 31) == 0) mask[id >> 5] = (uint32_t)(bits >> lane);
+    } else if (sel) {
+      __hip_atomic_fetch_or(mask + (id >> 5), 1u << (id & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
 }
 
-// compact arrays in caller order: position relative to the centre, velocity,
-// mass; pos holds the exclusive scan of the flags
+__global__ void __launch_bounds__(256)
+    k_disc_popc(const uint32_t* __restrict__ mask, int64_t words, uint32_t* __restrict__ cnt) {
+  const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (w <= words) cnt[w] = w < words ? (uint32_t)__popc(mask[w]) : 0u;
+}
+
+// One disc particle as it is held: x, y, z, vx, vy, vz, m, and its place in
+// its radial bucket (bits).
 template <typename T>
-__global__ void k_disc_compact(PartDev<T> p, int comp, int gal, const uint32_t* __restrict__ pos,
-                               const double* __restrict__ centre, double* __restrict__ d3,
-                               double* __restrict__ v3, double* __restrict__ m1) {
-  const double cx = centre[0], cy = centre[1], cz = centre[2];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+struct alignas(16) DiscRec {
+  T v[8];
+};
+template <typename T>
+__device__ __forceinline__ T put_bits(uint32_t u) {
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, u);
+  else return __builtin_bit_cast(T, (uint64_t)u);
+}
+__device__ __forceinline__ uint32_t get_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ uint32_t get_bits(double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); }
+
+template <typename T>
+__device__ __forceinline__ DiscRec<T> load_rec(const DiscRec<T>* __restrict__ rec, size_t k) {
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int W = 16 / sizeof(T);
+  DiscRec<T> r;
+  const gp<const vec> s = glb((const vec*)(rec + k));
+#pragma unroll
+  for (int q = 0; q < 8 / W; ++q) {
+    const vec x = s[q];
+#pragma unroll
+    for (int e = 0; e < W; ++e) r.v[q * W + e] = x[e];
+  }
+  return r;
+}
+
+// The galaxy's centre: of the last solve (on the device), else as given.
+struct Centre {
+  const double* dev;
+  double c[3];
+  __device__ __forceinline__ double at(int k) const { return dev ? dev[k] : c[k]; }
+};
+
+// Cylindrical radius, each operation rounded (the radial order depends on it).
+__device__ __forceinline__ double cyl_r(double dx, double dy) {
+#pragma clang fp contract(off)
+  return sqrt(dx * dx + dy * dy);
+}
+
+// Radial buckets: 2^bits per octave of R over 24 octaves up to `top`, what
+// lies outside in the first and the last; a bucket's radii are all below the
+// next one's.
+struct Buckets {
+  int base, shift, count;
+  __device__ __forceinline__ int of(double r) const {
+    const int hi = (int)(__double_as_longlong(r) >> 32) - base;
+    const int b = hi < 0 ? 0 : hi >> shift;
+    return b < count ? b : count - 1;
+  }
+};
+
+// Records in the caller's order; each particle takes a place in its bucket.
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_disc_compact(PartDev<T> p, int comp, int gal, const uint32_t* __restrict__ mask,
+                   const uint32_t* __restrict__ cnt, Centre cen, Buckets bk, uint32_t* __restrict__ fill,
+                   DiscRec<T>* __restrict__ rec) {
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int W = 16 / sizeof(T);
+  const double cx = cen.at(0), cy = cen.at(1);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * 256) {
     if (!(p.comp[i] == comp && p.gal[i] == gal && !p.lost[i])) continue;
-    const uint32_t k = pos[p.id[i]];
-    d3[3 * k] = (double)p.x[0][i] - cx;
-    d3[3 * k + 1] = (double)p.x[1][i] - cy;
-    d3[3 * k + 2] = (double)p.x[2][i] - cz;
-    v3[3 * k] = (double)p.v[0][i];
-    v3[3 * k + 1] = (double)p.v[1][i];
-    v3[3 * k + 2] = (double)p.v[2][i];
-    m1[k] = (double)p.m[i];
+    const uint32_t id = (uint32_t)p.id[i];
+    DiscRec<T> r;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      r.v[k] = p.x[k][i];
+      r.v[3 + k] = p.v[k][i];
+    }
+    r.v[6] = p.m[i];
+    const uint32_t k = cnt[id >> 5] + (uint32_t)__popc(mask[id >> 5] & ((1u << (id & 31)) - 1u));
+    const int b = bk.of(cyl_r((double)r.v[0] - cx, (double)r.v[1] - cy));
+    r.v[7] = put_bits<T>(__hip_atomic_fetch_add(fill + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const gp<vec> d = glb((vec*)(rec + k));
+#pragma unroll
+    for (int q = 0; q < 8 / W; ++q) {
+      vec x;
+#pragma unroll
+      for (int e = 0; e < W; ++e) x[e] = r.v[q * W + e];
+      d[q] = x;
+    }
   }
 }
 
@@ -69,21 +160,6 @@ __device__ __forceinline__ void block_rows(const double* vals, double* out) {
   for (int k = threadIdx.x; k < NV; k += blockDim.x) out[k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
 }
 
-// sums of m and m v over the disc (block partials)
-__global__ void __launch_bounds__(256)
-    k_disc_bulk(const double* __restrict__ v3, const double* __restrict__ m1, int64_t n,
-                double* __restrict__ part) {
-  double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double m = m1[i];
-    a[0] += m;
-    a[1] += m * v3[3 * i];
-    a[2] += m * v3[3 * i + 1];
-    a[3] += m * v3[3 * i + 2];
-  }
-  block_rows<4>(a, part + 4 * (size_t)blockIdx.x);
-}
-
 // column sums of rows x nv partials (one block per column, fixed order)
 __global__ void __launch_bounds__(256)
     k_columns(const double* __restrict__ part, int rows, int nv, double* __restrict__ out) {
@@ -100,25 +176,128 @@ __global__ void __launch_bounds__(256)
   if (threadIdx.x == 0) out[c] = red[0];
 }
 
-// cylindrical quantities relative to the disc's mean velocity; radix key of R
-__global__ void k_disc_cyl(const double* __restrict__ d3, const double* __restrict__ v3,
-                           const double* __restrict__ bulk, int64_t n, double* __restrict__ R,
-                           double* __restrict__ vR, double* __restrict__ vphi,
-                           double* __restrict__ vz, uint64_t* __restrict__ key,
-                           uint32_t* __restrict__ val) {
+// Radial key (R >= 0: the bits order like the values) and number of a particle.
+struct alignas(16) RadKey {
+  uint64_t r;
+  uint32_t k, pad;
+};
+
+// The records in order: keys to their buckets (start: the scanned counts),
+// and the sums of m and m v over the disc (block partials).
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_disc_keys(const DiscRec<T>* __restrict__ rec, int64_t n, Centre cen, Buckets bk,
+                const uint32_t* __restrict__ start, RadKey* __restrict__ key, double* __restrict__ part) {
+  const double cx = cen.at(0), cy = cen.at(1);
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const DiscRec<T> r = load_rec(rec, i);
+    const double R = cyl_r((double)r.v[0] - cx, (double)r.v[1] - cy);
+    const double m = (double)r.v[6];
+    a[0] += m;
+    a[1] += m * (double)r.v[3];
+    a[2] += m * (double)r.v[4];
+    a[3] += m * (double)r.v[5];
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const uint64_t u = (uint64_t)__double_as_longlong(R);
+    glb((u4*)key)[start[bk.of(R)] + get_bits(r.v[7])] = u4{(uint32_t)u, (uint32_t)(u >> 32), (uint32_t)i, 0u};
+  }
+  block_rows<4>(a, part + 4 * (size_t)blockIdx.x);
+}
+
+// Every bucket sorted by (radius, number): its keys in the wavefront's LDS,
+// a key's place the number of smaller ones.  Buckets of more than kBucketCap
+// raise the flag and leave their part of the order unset: what reads the
+// order does nothing while the flag stands, and the radix sort below then
+// orders the whole disc.  Bound by the chain of each bucket (bounds, keys,
+// comparisons): with a bucket per 64, 128 and 256 particles the whole call
+// took 1.00, 0.97 and 1.01 ms.  Eight 8-bit radix passes of the 64-bit radii
+// took 590 us for 2M particles; scattering the keys and this take 98 us.
+constexpr int kBucketCap = 768;  // 36 KB of LDS a block: four on a CU
+__global__ void __launch_bounds__(256)
+    k_disc_order(const RadKey* __restrict__ key, const uint32_t* __restrict__ start, int buckets,
+                 uint64_t* __restrict__ skey, uint32_t* __restrict__ order, uint32_t* __restrict__ flag) {
+  __shared__ uint64_t rs[4][kBucketCap];
+  __shared__ uint32_t ks[4][kBucketCap];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t* const R = rs[wave];
+  uint32_t* const K = ks[wave];
+  for (int b = (int)blockIdx.x * 4 + wave; b < buckets; b += (int)gridDim.x * 4) {
+    const uint32_t s0 = start[b];
+    const int m = (int)(start[b + 1] - s0);
+    if (m == 0) continue;
+    if (m > kBucketCap) {
+      if (lane == 0) *flag = 1u;
+      continue;
+    }
+    for (int e = lane; e < m; e += 64) {
+      const RadKey q = key[s0 + e];
+      R[e] = q.r;
+      K[e] = q.k;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int e0 = 0; e0 < m; e0 += 128) {  // two keys a lane per walk
+      const int ea = e0 + lane, eb = ea + 64;
+      const uint64_t ra = R[ea < m ? ea : 0], rb = R[eb < m ? eb : 0];
+      const uint32_t ka = K[ea < m ? ea : 0], kb = K[eb < m ? eb : 0];
+      uint32_t pa = 0, pb = 0;
+#pragma unroll 4
+      for (int j = 0; j < m; ++j) {
+        const uint64_t rj = R[j];
+        const uint32_t kj = K[j];
+        pa += (rj < ra || (rj == ra && kj < ka)) ? 1u : 0u;
+        pb += (rj < rb || (rj == rb && kj < kb)) ? 1u : 0u;
+      }
+      if (ea < m) {
+        skey[s0 + pa] = ra;
+        order[s0 + pa] = ka;
+      }
+      if (eb < m) {
+        skey[s0 + pb] = rb;
+        order[s0 + pb] = kb;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// Cylindrical quantities of a record relative to the disc's mean velocity.
+struct Cyl {
+  double R, vR, vphi, vz, dz;
+};
+template <typename T>
+__device__ __forceinline__ Cyl cyl_of(const DiscRec<T>& r, const double* c, const double* b) {
 #pragma clang fp contract(off)
-  const double M = bulk[0];
-  const double bx = bulk[1] / M, by = bulk[2] / M, bz = bulk[3] / M;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double dx = d3[3 * i], dy = d3[3 * i + 1];
-    const double ux = v3[3 * i] - bx, uy = v3[3 * i + 1] - by, uz = v3[3 * i + 2] - bz;
-    const double r = sqrt(dx * dx + dy * dy);
-    R[i] = r;
-    vR[i] = r > 0.0 ? (dx * ux + dy * uy) / r : 0.0;
-    vphi[i] = r > 0.0 ? (dx * uy - dy * ux) / r : 0.0;
-    vz[i] = uz;
-    key[i] = (uint64_t)__double_as_longlong(r);  // R >= 0: bit order is value order
+  Cyl o;
+  const double dx = (double)r.v[0] - c[0], dy = (double)r.v[1] - c[1];
+  const double ux = (double)r.v[3] - b[0], uy = (double)r.v[4] - b[1];
+  o.R = cyl_r(dx, dy);
+  o.vR = o.R > 0.0 ? (dx * ux + dy * uy) / o.R : 0.0;
+  o.vphi = o.R > 0.0 ? (dx * uy - dy * ux) / o.R : 0.0;
+  o.vz = (double)r.v[5] - b[2];
+  o.dz = (double)r.v[2] - c[2];
+  return o;
+}
+__device__ __forceinline__ void frame(const Centre& cen, const double* bulk, double* c, double* b) {
+  for (int k = 0; k < 3; ++k) {
+    c[k] = cen.at(k);
+    b[k] = bulk ? bulk[1 + k] / bulk[0] : 0.0;
+  }
+}
+
+// keys of the whole disc in the caller's order, for the radix sort
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_disc_radii(const DiscRec<T>* __restrict__ rec, int64_t n, Centre cen, uint64_t* __restrict__ key,
+                 uint32_t* __restrict__ val) {
+  const double cx = cen.at(0), cy = cen.at(1);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const DiscRec<T> r = load_rec(rec, i);
+    key[i] = (uint64_t)__double_as_longlong(cyl_r((double)r.v[0] - cx, (double)r.v[1] - cy));
     val[i] = (uint32_t)i;
   }
 }
@@ -182,42 +361,52 @@ __global__ void __launch_bounds__(64)
 }
 
 // ------------------------------------------------------------------- bins --
-// one block per bin: mean R, mean v_phi, RMS z over the bin's range of the
-// sorted order (bin k: n / nbins items, plus one for k < n % nbins)
+// mean R, mean v_phi, RMS z over a bin's range of the sorted order (bin k:
+// n / nbins items, plus one for k < n % nbins).  A bin is split over
+// gridDim.y blocks (one block a bin left most of the chip idle), whose sums
+// are added in order by k_disc_bins_end.
+template <typename T>
 __global__ void __launch_bounds__(256)
-    k_disc_bins(const uint32_t* __restrict__ order, int64_t n, int nbins, const double* __restrict__ R,
-                const double* __restrict__ vphi, const double* __restrict__ d3,
-                double* __restrict__ bin_r, double* __restrict__ bin_vc, double* __restrict__ bin_rz) {
+    k_disc_bins(const uint32_t* __restrict__ order, int64_t n, int nbins, const DiscRec<T>* __restrict__ rec,
+                Centre cen, const double* __restrict__ bulk, const uint32_t* __restrict__ flag,
+                double* __restrict__ part) {
+  if (*flag) return;  // no order yet
   const int k = blockIdx.x;
   const int64_t q = n / nbins, r = n % nbins;
   const int64_t s0 = k * q + (k < r ? k : r);
   const int64_t s1 = s0 + q + (k < r ? 1 : 0);
+  double c[3], b[3];
+  frame(cen, bulk, c, b);
   double a[3] = {0.0, 0.0, 0.0};
-  for (int64_t j = s0 + threadIdx.x; j < s1; j += 256) {
-    const uint32_t i = order[j];
-    const double z = d3[3 * (size_t)i + 2];
-    a[0] += R[i];
-    a[1] += vphi[i];
-    a[2] += z * z;
+  for (int64_t j = s0 + (int64_t)blockIdx.y * 256 + threadIdx.x; j < s1; j += (int64_t)gridDim.y * 256) {
+    const Cyl y = cyl_of(load_rec(rec, order[j]), c, b);
+    a[0] += y.R;
+    a[1] += y.vphi;
+    a[2] += y.dz * y.dz;
   }
-  __shared__ double out[3];
-  block_rows<3>(a, out);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double c = (double)(s1 - s0);
-    bin_r[k] = c > 0 ? out[0] / c : 0.0;
-    bin_vc[k] = c > 0 ? out[1] / c : 0.0;
-    bin_rz[k] = c > 0 ? sqrt(out[2] / c) : 0.0;
-  }
+  block_rows<3>(a, part + 3 * ((size_t)k * gridDim.y + blockIdx.y));
+}
+
+__global__ void __launch_bounds__(256)
+    k_disc_bins_end(const double* __restrict__ part, int split, int64_t n, int nbins,
+                    double* __restrict__ bin_r, double* __restrict__ bin_vc, double* __restrict__ bin_rz) {
+  const int k = (int)blockIdx.x * 256 + threadIdx.x;
+  if (k >= nbins) return;
+  double s[3] = {0.0, 0.0, 0.0};
+  for (int q = 0; q < split; ++q)
+    for (int e = 0; e < 3; ++e) s[e] += part[3 * ((size_t)k * split + q) + e];
+  const double c = (double)(n / nbins + (k < n % nbins ? 1 : 0));
+  bin_r[k] = c > 0 ? s[0] / c : 0.0;
+  bin_vc[k] = c > 0 ? s[1] / c : 0.0;
+  bin_rz[k] = c > 0 ? sqrt(s[2] / c) : 0.0;
 }
 
 // heat with the interpolated circular velocity; annulus sums; z profile
+template <typename T>
 __global__ void __launch_bounds__(256)
     k_disc_heat(int64_t n, int nbins, const double* __restrict__ bin_r, const double* __restrict__ bin_vc,
-                const double* __restrict__ R, const double* __restrict__ vR,
-                const double* __restrict__ vphi, const double* __restrict__ vz,
-                const double* __restrict__ d3, const double* __restrict__ m1, double lo, double hi,
-                int nz, double zmax, double* __restrict__ part, double* __restrict__ zpart) {
+                const DiscRec<T>* __restrict__ rec, Centre cen, const double* __restrict__ bulk, double lo,
+                double hi, int nz, double zmax, double* __restrict__ part, double* __restrict__ zpart) {
   extern __shared__ double sh[];  // bin_r, bin_vc (nbins each), then nz profile bins
   double* br = sh;
   double* bv = sh + nbins;
@@ -227,11 +416,15 @@ __global__ void __launch_bounds__(256)
     bv[k] = bin_vc[k];
   }
   for (int k = threadIdx.x; k < nz; k += 256) hz[k] = 0.0;
+  double cc[3], bb[3];
+  frame(cen, bulk, cc, bb);
   __syncthreads();
   const double dz = 2.0 * zmax / nz;
   double a[kAnVals] = {};
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double r = R[i], m = m1[i];
+    const DiscRec<T> rc = load_rec(rec, i);
+    const Cyl y = cyl_of(rc, cc, bb);
+    const double r = y.R, m = (double)rc.v[6];
     // vbar_c(r): linear between the bins' mean radii, constant beyond the ends
     double vc;
     if (r <= br[0]) {
@@ -248,7 +441,7 @@ __global__ void __launch_bounds__(256)
       const double t = (r - br[lo_k]) / (br[hi_k] - br[lo_k]);
       vc = bv[lo_k] + t * (bv[hi_k] - bv[lo_k]);
     }
-    const double a_r = vR[i], a_p = vphi[i], a_z = vz[i];
+    const double a_r = y.vR, a_p = y.vphi, a_z = y.vz;
     const double dp = a_p - vc;
     a[0] += 0.5 * m * ((a_r * a_r + dp * dp) + a_z * a_z);
     if (r >= lo && r < hi) {
@@ -259,7 +452,7 @@ __global__ void __launch_bounds__(256)
       a[5] += a_p * a_p;
       a[6] += a_z;
       a[7] += a_z * a_z;
-      const double z = d3[3 * i + 2];
+      const double z = y.dz;
       if (z >= -zmax && z < zmax) {
         int k = (int)floor((z + zmax) / dz);
         k = k < nz - 1 ? k : nz - 1;
@@ -289,91 +482,160 @@ PartDev<T> live_set(sbx_ctx* c) {
   return p;
 }
 
-// Device buffers of a prepared disc: compact arrays in caller order and the
-// radial order.  Freed together.
-struct Disc {
-  std::vector<void*> allocs;
-  int64_t n = 0;
-  double *d3 = nullptr, *v3 = nullptr, *m1 = nullptr, *bulk = nullptr;
-  double *R = nullptr, *vR = nullptr, *vphi = nullptr, *vz = nullptr;
-  uint64_t* key = nullptr;    // sorted radius keys (FP64 bits)
-  uint32_t* order = nullptr;  // compact index of the sorted positions
-  sbx_status alloc(void** p, size_t bytes) {
-    const sbx_status r = dev_alloc(p, bytes ? bytes : 8);
-    if (r == SBX_OK) allocs.push_back(*p);
-    return r;
+// Work arrays carved from one device buffer of the context, kept between
+// calls and grown when a call needs more (allocating and freeing some
+// fifteen arrays took over half of a call).
+struct Arena {
+  sbx_ctx* c;
+  size_t at = 0;
+  size_t take(size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) & ~(size_t)255;
+    return o;
   }
-  ~Disc() {
-    for (void* q : allocs) (void)hipFree(q);
+  sbx_status reserve() {
+    if (c->an_work_bytes >= at) return SBX_OK;
+    SBX_HIP(hipStreamSynchronize(c->stream));
+    free_ptr(c->an_work);
+    c->an_work_bytes = 0;
+    SBX_TRY(dev_alloc(&c->an_work, at));
+    c->an_work_bytes = at;
+    return SBX_OK;
+  }
+  template <typename P>
+  P* ptr(size_t o) const {
+    return (P*)((char*)c->an_work + o);
   }
 };
 
-// Select the disc (caller order), centre it on the galaxy, take velocities
-// relative to its mean, compute cylindrical quantities, sort by radius.
+// A prepared disc: records in the caller's order and the radial order.
 template <typename T>
-sbx_status disc_prepare(sbx_ctx* c, int comp, int galaxy, Disc& D) {
-  const int64_t n = c->n;
+struct Disc {
+  int64_t n = 0;
+  DiscRec<T>* rec = nullptr;
+  uint64_t* key = nullptr;    // sorted radius keys (FP64 bits)
+  uint32_t* order = nullptr;  // number of the particle at each sorted place
+  uint64_t* key2 = nullptr;   // the radix sort's other buffers
+  uint32_t *order2 = nullptr, *cnt = nullptr, *ctmp = nullptr;
+  double* bulk = nullptr;
+  uint32_t* flag = nullptr;   // set when a bucket was too full: radix sort
+  void* extra = nullptr;      // the caller's own part of the work buffer
+  Centre cen;
+};
+
+int rs_blocks(int64_t n) { return (int)((n + kRsTile - 1) / kRsTile); }
+
+// Select the disc (caller order), centre it on the galaxy, sort by radius.
+// extra: bytes of work the caller wants for itself.
+template <typename T>
+sbx_status disc_prepare(sbx_ctx* c, int comp, int galaxy, size_t extra, Disc<T>& D) {
+  const int64_t n = c->n, words = (n + 31) / 32;
   hipStream_t s = c->stream;
   const PartDev<T> p = live_set<T>(c);
-  uint32_t *flag = nullptr, *tmp = nullptr;
-  SBX_TRY(D.alloc((void**)&flag, sizeof(uint32_t) * (n + 1)));
-  SBX_TRY(D.alloc((void**)&tmp, sizeof(uint32_t) * scan_tmp_elems(n + 1)));
-  SBX_TRY(launch_zero<uint32_t>(flag, n + 1, s));
-  hipLaunchKernelGGL((k_disc_flags<T>), dim3(1024), dim3(256), 0, s, p, comp, galaxy, flag);
-  SBX_TRY(exclusive_scan_u32(flag, n + 1, tmp, s));
+  D.cen.dev = c->solved ? c->centres + 3 * galaxy : nullptr;
+  for (int k = 0; k < 3; ++k) D.cen.c[k] = c->hh[galaxy].centre[k];
+  Arena A{c};
+  const size_t o_mask = A.take(4 * words), o_cnt = A.take(4 * (words + 1));
+  const size_t o_tmp = A.take(4 * scan_tmp_elems(words + 1));
+  SBX_TRY(A.reserve());
   uint32_t nd32 = 0;
-  SBX_HIP(hipMemcpyAsync(&nd32, flag + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  SBX_HIP(hipStreamSynchronize(s));
+  {
+    uint32_t* mask = A.ptr<uint32_t>(o_mask);
+    uint32_t* cnt = A.ptr<uint32_t>(o_cnt);
+    SBX_TRY(launch_zero<uint32_t>(mask, words, s));
+    hipLaunchKernelGGL((k_disc_mask<T>), dim3(2048), dim3(256), 0, s, p, comp, galaxy, mask);
+    hipLaunchKernelGGL(k_disc_popc, dim3((unsigned)(words / 256 + 1)), dim3(256), 0, s, mask, words, cnt);
+    SBX_TRY(exclusive_scan_u32(cnt, words + 1, A.ptr<uint32_t>(o_tmp), s));
+    SBX_HIP(hipMemcpyAsync(&nd32, cnt + words, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    SBX_HIP(hipStreamSynchronize(s));
+  }
   const int64_t nd = nd32;
   D.n = nd;
   if (nd == 0) {
     set_error("no live particles of the requested disc component");
     return SBX_ESTATE;
   }
-  // centre of the galaxy's grids at the last solve (else its given centre)
-  double cen[3];
-  for (int k = 0; k < 3; ++k) cen[k] = c->hh[galaxy].centre[k];
-  if (c->solved) SBX_HIP(hipMemcpy(cen, c->centres + 3 * galaxy, sizeof(cen), hipMemcpyDeviceToHost));
-  double *dcen = nullptr, *part = nullptr;
-  SBX_TRY(D.alloc((void**)&dcen, sizeof(cen)));
-  SBX_HIP(hipMemcpyAsync(dcen, cen, sizeof(cen), hipMemcpyHostToDevice, s));
-  SBX_TRY(D.alloc((void**)&D.d3, sizeof(double) * 3 * nd));
-  SBX_TRY(D.alloc((void**)&D.v3, sizeof(double) * 3 * nd));
-  SBX_TRY(D.alloc((void**)&D.m1, sizeof(double) * nd));
-  hipLaunchKernelGGL((k_disc_compact<T>), dim3(1024), dim3(256), 0, s, p, comp, galaxy, flag, dcen, D.d3,
-                     D.v3, D.m1);
-  SBX_TRY(D.alloc((void**)&part, sizeof(double) * 1024 * 4));
-  SBX_TRY(D.alloc((void**)&D.bulk, sizeof(double) * 4));
-  hipLaunchKernelGGL(k_disc_bulk, dim3(1024), dim3(256), 0, s, D.v3, D.m1, nd, part);
-  hipLaunchKernelGGL(k_columns, dim3(4), dim3(256), 0, s, part, 1024, 4, D.bulk);
-  uint64_t* kb = nullptr;
-  uint32_t *vb = nullptr, *cnt = nullptr, *ctmp = nullptr;
-  SBX_TRY(D.alloc((void**)&D.R, sizeof(double) * nd));
-  SBX_TRY(D.alloc((void**)&D.vR, sizeof(double) * nd));
-  SBX_TRY(D.alloc((void**)&D.vphi, sizeof(double) * nd));
-  SBX_TRY(D.alloc((void**)&D.vz, sizeof(double) * nd));
-  SBX_TRY(D.alloc((void**)&D.key, sizeof(uint64_t) * nd));
-  SBX_TRY(D.alloc((void**)&kb, sizeof(uint64_t) * nd));
-  SBX_TRY(D.alloc((void**)&D.order, sizeof(uint32_t) * nd));
-  SBX_TRY(D.alloc((void**)&vb, sizeof(uint32_t) * nd));
-  hipLaunchKernelGGL(k_disc_cyl, dim3(1024), dim3(256), 0, s, D.d3, D.v3, D.bulk, nd, D.R, D.vR, D.vphi,
-                     D.vz, D.key, D.order);
-  const int nb = (int)((nd + kRsTile - 1) / kRsTile);
+  // about 2^bits = nd / 256 buckets per octave of the radius: near the peak of
+  // a disc they hold some 200 particles; the top octave holds the far corner
+  // of the grid
+  int bits = 4;
+  while (bits < 15 && (nd >> (bits + 8)) > 0) ++bits;
+  const double span = c->hh[galaxy].lv[c->hh[galaxy].n_levels - 1].R;
+  const int top = std::min(1023 + 1000, std::max(24, 1023 + std::ilogb(span) + 3));
+  const Buckets bk{(top - 24) << 20, 20 - bits, 24 << bits};
+  const int nb = rs_blocks(nd);
   const size_t ncnt = (size_t)256 * nb;
-  SBX_TRY(D.alloc((void**)&cnt, sizeof(uint32_t) * ncnt));
-  SBX_TRY(D.alloc((void**)&ctmp, sizeof(uint32_t) * scan_tmp_elems(ncnt)));
-  uint64_t* ka = D.key;
-  uint32_t* va = D.order;
-  for (int shift = 0; shift < 64; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(64), 0, s, ka, nd, shift, nb, cnt);
-    SBX_TRY(exclusive_scan_u32(cnt, ncnt, ctmp, s));
-    hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(64), 0, s, ka, va, nd, shift, nb, cnt, kb, vb);
+  const size_t o_fill = A.take(4 * ((size_t)bk.count + 1)), o_ftmp = A.take(4 * scan_tmp_elems(bk.count + 1));
+  const size_t o_flag = A.take(4), o_rec = A.take(sizeof(DiscRec<T>) * nd);
+  const size_t o_key = A.take(16 * nd);  // bucketed keys; the radix sort's second buffers and counts
+  const size_t o_skey = A.take(8 * nd), o_ord = A.take(4 * nd);
+  const size_t o_rcnt = A.take(4 * ncnt), o_rtmp = A.take(4 * scan_tmp_elems(ncnt));
+  const size_t o_part = A.take(sizeof(double) * 4 * kBulkBlocks), o_bulk = A.take(sizeof(double) * 4);
+  const size_t o_extra = A.take(extra);
+  const bool grow = c->an_work_bytes < A.at;
+  SBX_TRY(A.reserve());
+  if (grow) return disc_prepare<T>(c, comp, galaxy, extra, D);  // a new buffer: select again
+  uint32_t* fill = A.ptr<uint32_t>(o_fill);
+  D.rec = A.ptr<DiscRec<T>>(o_rec);
+  D.key = A.ptr<uint64_t>(o_skey);
+  D.order = A.ptr<uint32_t>(o_ord);
+  D.key2 = A.ptr<uint64_t>(o_key);
+  D.order2 = (uint32_t*)(D.key2 + nd);
+  D.cnt = A.ptr<uint32_t>(o_rcnt);
+  D.ctmp = A.ptr<uint32_t>(o_rtmp);
+  D.bulk = A.ptr<double>(o_bulk);
+  D.flag = A.ptr<uint32_t>(o_flag);
+  D.extra = A.ptr<void>(o_extra);
+  double* part = A.ptr<double>(o_part);
+  // counts and flag cleared together (they are neighbours)
+  SBX_TRY(launch_zero<uint32_t>(fill, (o_flag - o_fill) / 4 + 1, s));
+  hipLaunchKernelGGL((k_disc_compact<T>), dim3(4096), dim3(256), 0, s, p, comp, galaxy,
+                     A.ptr<uint32_t>(o_mask), A.ptr<uint32_t>(o_cnt), D.cen, bk, fill, D.rec);
+  SBX_TRY(exclusive_scan_u32(fill, (size_t)bk.count + 1, A.ptr<uint32_t>(o_ftmp), s));
+  hipLaunchKernelGGL((k_disc_keys<T>), dim3(kBulkBlocks), dim3(256), 0, s, D.rec, nd, D.cen, bk, fill,
+                     A.ptr<RadKey>(o_key), part);
+  hipLaunchKernelGGL(k_columns, dim3(4), dim3(256), 0, s, part, kBulkBlocks, 4, D.bulk);
+  hipLaunchKernelGGL(k_disc_order, dim3(4096), dim3(256), 0, s, A.ptr<RadKey>(o_key), fill, bk.count, D.key,
+                     D.order, D.flag);
+  SBX_HIP(hipGetLastError());
+  return SBX_OK;
+}
+
+// The radial order by a stable radix sort of the whole disc (radii too
+// crowded for the buckets).
+template <typename T>
+sbx_status disc_radix(sbx_ctx* c, const Disc<T>& D) {
+  hipStream_t s = c->stream;
+  const int nb = rs_blocks(D.n);
+  hipLaunchKernelGGL((k_disc_radii<T>), dim3(1024), dim3(256), 0, s, D.rec, D.n, D.cen, D.key, D.order);
+  uint64_t *ka = D.key, *kb = D.key2;
+  uint32_t *va = D.order, *vb = D.order2;
+  for (int shift = 0; shift < 64; shift += 8) {  // eight passes: the result is back in the first buffers
+    hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(64), 0, s, ka, D.n, shift, nb, D.cnt);
+    SBX_TRY(exclusive_scan_u32(D.cnt, (size_t)256 * nb, D.ctmp, s));
+    hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(64), 0, s, ka, va, D.n, shift, nb, D.cnt, kb, vb);
     std::swap(ka, kb);
     std::swap(va, vb);
   }
-  D.key = ka;  // eight passes: the sorted data is back in the first buffers
-  D.order = va;
+  SBX_TRY(launch_zero<uint32_t>(D.flag, 1, s));  // the order stands
   SBX_HIP(hipGetLastError());
+  return SBX_OK;
+}
+
+// Run `use(buf)`, which queues the passes that need the radial order and
+// leaves `count` doubles at buf, and copy them to out; if the buckets
+// overflowed, once more on the radix sort's order.
+template <typename T, typename Fn>
+sbx_status with_order(sbx_ctx* c, const Disc<T>& D, double* buf, size_t count, double* out, Fn&& use) {
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    SBX_TRY(use());
+    uint32_t flag = 0;
+    SBX_HIP(hipMemcpyAsync(out, buf, sizeof(double) * count, hipMemcpyDeviceToHost, c->stream));
+    if (attempt == 0) SBX_HIP(hipMemcpyAsync(&flag, D.flag, sizeof(flag), hipMemcpyDeviceToHost, c->stream));
+    SBX_HIP(hipStreamSynchronize(c->stream));
+    if (!flag) break;
+    SBX_TRY(disc_radix<T>(c, D));
+  }
   return SBX_OK;
 }
 
@@ -381,38 +643,40 @@ template <typename T>
 sbx_status disc_t(sbx_ctx* c, const sbx_disc_query* qy, sbx_disc_result* res, double* bin_r,
                   double* bin_vc, double* bin_rms_z, double* rho_z) {
   hipStream_t s = c->stream;
-  Disc D;
+  Disc<T> D;
+  const int nbins = qy->n_bins, nz = qy->n_z;
+  const int split = std::max(1, std::min(32, 2048 / nbins));
+  // results [annulus and heat 8][bulk 4][profile nz][bin r, vc, rms z], then partials
+  const size_t nres = kAnVals + 4 + nz + 3 * (size_t)nbins;
+  const size_t npart = 3 * (size_t)nbins * split + (size_t)kAnBlocks * (kAnVals + nz);
   auto body = [&]() -> sbx_status {
-    SBX_TRY(disc_prepare<T>(c, qy->comp, qy->galaxy, D));
+    SBX_TRY(disc_prepare<T>(c, qy->comp, qy->galaxy, sizeof(double) * (nres + npart), D));
     const int64_t nd = D.n;
     res->n_disc = nd;
-    const int nbins = qy->n_bins;
-    double *br = nullptr, *bv = nullptr, *bz = nullptr, *apart = nullptr, *zpart = nullptr,
-           *asum = nullptr, *zsum = nullptr;
-    SBX_TRY(D.alloc((void**)&br, sizeof(double) * nbins));
-    SBX_TRY(D.alloc((void**)&bv, sizeof(double) * nbins));
-    SBX_TRY(D.alloc((void**)&bz, sizeof(double) * nbins));
-    hipLaunchKernelGGL(k_disc_bins, dim3(nbins), dim3(256), 0, s, D.order, nd, nbins, D.R, D.vphi, D.d3, br,
-                       bv, bz);
-    SBX_TRY(D.alloc((void**)&apart, sizeof(double) * kAnBlocks * kAnVals));
-    SBX_TRY(D.alloc((void**)&zpart, sizeof(double) * kAnBlocks * qy->n_z));
-    SBX_TRY(D.alloc((void**)&asum, sizeof(double) * kAnVals));
-    SBX_TRY(D.alloc((void**)&zsum, sizeof(double) * qy->n_z));
-    const size_t shb = sizeof(double) * (2 * (size_t)nbins + qy->n_z);
-    hipLaunchKernelGGL(k_disc_heat, dim3(kAnBlocks), dim3(256), shb, s, nd, nbins, br, bv, D.R, D.vR, D.vphi,
-                       D.vz, D.d3, D.m1, qy->annulus[0], qy->annulus[1], qy->n_z, qy->z_max, apart, zpart);
-    hipLaunchKernelGGL(k_columns, dim3(kAnVals), dim3(256), 0, s, apart, kAnBlocks, kAnVals, asum);
-    hipLaunchKernelGGL(k_columns, dim3(qy->n_z), dim3(256), 0, s, zpart, kAnBlocks, qy->n_z, zsum);
-    SBX_HIP(hipGetLastError());
-    double a[kAnVals], b4[4];
-    std::vector<double> z(qy->n_z);
-    SBX_HIP(hipMemcpyAsync(a, asum, sizeof(a), hipMemcpyDeviceToHost, s));
-    SBX_HIP(hipMemcpyAsync(b4, D.bulk, sizeof(b4), hipMemcpyDeviceToHost, s));
-    SBX_HIP(hipMemcpyAsync(z.data(), zsum, sizeof(double) * qy->n_z, hipMemcpyDeviceToHost, s));
-    if (bin_r) SBX_HIP(hipMemcpyAsync(bin_r, br, sizeof(double) * nbins, hipMemcpyDeviceToHost, s));
-    if (bin_vc) SBX_HIP(hipMemcpyAsync(bin_vc, bv, sizeof(double) * nbins, hipMemcpyDeviceToHost, s));
-    if (bin_rms_z) SBX_HIP(hipMemcpyAsync(bin_rms_z, bz, sizeof(double) * nbins, hipMemcpyDeviceToHost, s));
-    SBX_HIP(hipStreamSynchronize(s));
+    double* asum = (double*)D.extra;
+    double *bsum = asum + kAnVals, *zsum = bsum + 4;
+    double *br = zsum + nz, *bv = br + nbins, *bz = bv + nbins;
+    double *bpart = bz + nbins, *apart = bpart + 3 * (size_t)nbins * split;
+    double* zpart = apart + (size_t)kAnBlocks * kAnVals;
+    std::vector<double> h(nres);
+    const size_t shb = sizeof(double) * (2 * (size_t)nbins + nz);
+    SBX_TRY(with_order<T>(c, D, asum, nres, h.data(), [&]() -> sbx_status {
+      SBX_HIP(hipMemcpyAsync(bsum, D.bulk, sizeof(double) * 4, hipMemcpyDeviceToDevice, s));
+      hipLaunchKernelGGL((k_disc_bins<T>), dim3(nbins, split), dim3(256), 0, s, D.order, nd, nbins, D.rec,
+                         D.cen, D.bulk, D.flag, bpart);
+      hipLaunchKernelGGL(k_disc_bins_end, dim3((nbins + 255) / 256), dim3(256), 0, s, bpart, split, nd, nbins,
+                         br, bv, bz);
+      hipLaunchKernelGGL((k_disc_heat<T>), dim3(kAnBlocks), dim3(256), shb, s, nd, nbins, br, bv, D.rec,
+                         D.cen, D.bulk, qy->annulus[0], qy->annulus[1], nz, qy->z_max, apart, zpart);
+      hipLaunchKernelGGL(k_columns, dim3(kAnVals), dim3(256), 0, s, apart, kAnBlocks, kAnVals, asum);
+      hipLaunchKernelGGL(k_columns, dim3(nz), dim3(256), 0, s, zpart, kAnBlocks, nz, zsum);
+      SBX_HIP(hipGetLastError());
+      return SBX_OK;
+    }));
+    const double *a = h.data(), *b4 = a + kAnVals, *z = b4 + 4, *hb = z + nz;
+    if (bin_r) std::copy(hb, hb + nbins, bin_r);
+    if (bin_vc) std::copy(hb + nbins, hb + 2 * nbins, bin_vc);
+    if (bin_rms_z) std::copy(hb + 2 * nbins, hb + 3 * nbins, bin_rms_z);
     res->e_heat = a[0];
     res->n_annulus = (int64_t)llround(a[1]);
     auto sd = [&](double s1, double s2) {
@@ -426,9 +690,9 @@ sbx_status disc_t(sbx_ctx* c, const sbx_disc_query* qy, sbx_disc_result* res, do
     res->sig_tot2 = res->sig_R * res->sig_R + res->sig_phi * res->sig_phi + res->sig_z * res->sig_z;
     for (int k = 0; k < 3; ++k) res->bulk_v[k] = b4[1 + k] / b4[0];
     const double lo = qy->annulus[0], hi = qy->annulus[1];
-    const double area = M_PI * (hi * hi - lo * lo), dz = 2.0 * qy->z_max / qy->n_z;
+    const double area = M_PI * (hi * hi - lo * lo), dz = 2.0 * qy->z_max / nz;
     if (rho_z)
-      for (int k = 0; k < qy->n_z; ++k) rho_z[k] = z[k] / (area * dz);
+      for (int k = 0; k < nz; ++k) rho_z[k] = z[k] / (area * dz);
     return SBX_OK;
   };
   const sbx_status rc = body();
@@ -449,52 +713,101 @@ __device__ __forceinline__ int64_t lower_bound_r(const uint64_t* key, int64_t n,
   return lo;
 }
 
-// One block per annular bin [k dR, (k+1) dR): sum over its particles of
-// M cos(m phi) and -M sin(m phi), m = 0..mmax, in a fixed order; divided by
-// the bin area.  out[(k * (mmax + 1) + m) * 2 + {0, 1}] = re, im.
+// Annular bin [k dR, (k+1) dR) split over gridDim.y blocks: sums over its
+// particles of M cos(m phi) and -M sin(m phi), m = 0..MM, in a fixed order.
+// The factors e^{i m phi} are products of e^{i phi} = (x + i y) / R, each of
+// at most log2(m) + 1 factors, so that their rounding stays that of the
+// angle itself; radii whose square leaves the normal range take the angle.
+// One block a bin and a sincos per m took 884 us for 2M particles, 64 bins
+// and m up to 4 (now 60 us).
+template <typename T, int MM>
 __global__ void __launch_bounds__(256)
     k_disc_modes(const uint64_t* __restrict__ key, const uint32_t* __restrict__ order, int64_t n,
-                 const double* __restrict__ d3, const double* __restrict__ m1, double dR, int mmax,
-                 double* __restrict__ out) {
-  constexpr int kMaxM = 16;
+                 const DiscRec<T>* __restrict__ rec, Centre cen, double dR, const uint32_t* __restrict__ flag,
+                 double* __restrict__ part) {
+  if (*flag) return;  // no order yet
   const int k = blockIdx.x;
   const int64_t s0 = lower_bound_r(key, n, k * dR), s1 = lower_bound_r(key, n, (k + 1) * dR);
-  double a[2 * (kMaxM + 1)] = {};
-  for (int64_t j = s0 + threadIdx.x; j < s1; j += 256) {
-    const uint32_t i = order[j];
-    const double ph = atan2(d3[3 * (size_t)i + 1], d3[3 * (size_t)i]);
-    const double m = m1[i];
+  const double cx = cen.at(0), cy = cen.at(1);
+  double a[2 * (MM + 1)] = {};
+  for (int64_t j = s0 + (int64_t)blockIdx.y * 256 + threadIdx.x; j < s1; j += (int64_t)gridDim.y * 256) {
+    const DiscRec<T> r = load_rec(rec, order[j]);
+    const double dx = (double)r.v[0] - cx, dy = (double)r.v[1] - cy;
+    const double m = (double)r.v[6];
+    double re[MM + 1], im[MM + 1];
+    re[0] = 1.0;
+    im[0] = 0.0;
+    if constexpr (MM > 0) {
+      const double R = __longlong_as_double((long long)key[j]);
+      if (R > 1e-140 && R < 1e140) {
+        re[1] = dx / R;
+        im[1] = dy / R;
+      } else {
+        sincos(atan2(dy, dx), &im[1], &re[1]);
+      }
 #pragma unroll
-    for (int q = 0; q <= kMaxM; ++q) {
-      if (q > mmax) break;
-      double sn, cs;
-      sincos((double)q * ph, &sn, &cs);
-      a[2 * q] += m * cs;
-      a[2 * q + 1] -= m * sn;
+      for (int q = 2; q <= MM; ++q) {
+        const int h = q / 2, g = q - h;
+        re[q] = re[h] * re[g] - im[h] * im[g];
+        im[q] = re[h] * im[g] + im[h] * re[g];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q <= MM; ++q) {
+      a[2 * q] += m * re[q];
+      a[2 * q + 1] -= m * im[q];
     }
   }
-  __shared__ double res[2 * (kMaxM + 1)];
-  block_rows<2 * (kMaxM + 1)>(a, res);
-  __syncthreads();
+  block_rows<2 * (MM + 1)>(a, part + ((size_t)k * gridDim.y + blockIdx.y) * 2 * (MM + 1));
+}
+
+// The blocks' sums of each bin added in order and divided by the bin area:
+// out[(k * (mmax + 1) + m) * 2 + {0, 1}] = re, im.
+__global__ void __launch_bounds__(256)
+    k_disc_modes_end(const double* __restrict__ part, int split, int width, int mmax, int nr, double dR,
+                     double* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int w = 2 * (mmax + 1);
+  if (i >= (int64_t)nr * w) return;
+  const int k = (int)(i / w), q = (int)(i - (int64_t)k * w);
+  double s = 0.0;
+#pragma unroll 8
+  for (int b = 0; b < split; ++b) s += part[((size_t)k * split + b) * width + q];
   const double S = M_PI * dR * dR * ((double)(k + 1) * (k + 1) - (double)k * k);
-  for (int q = threadIdx.x; q < 2 * (mmax + 1); q += 256) out[(size_t)k * 2 * (mmax + 1) + q] = res[q] / S;
+  out[i] = s / S;
 }
 
 template <typename T>
 sbx_status modes_t(sbx_ctx* c, int comp, int galaxy, int nr, double rmax, int mmax, double* coeff) {
   hipStream_t s = c->stream;
-  Disc D;
+  Disc<T> D;
+  const int split = std::max(1, std::min(64, 4096 / nr));
+  // sums for the least of 0, 2, 4, 8, 16 that covers mmax
+  const int MM = mmax == 0 ? 0 : mmax <= 2 ? 2 : mmax <= 4 ? 4 : mmax <= 8 ? 8 : 16;
+  const size_t width = 2 * (MM + 1), cnt = (size_t)nr * (mmax + 1) * 2;
   auto body = [&]() -> sbx_status {
-    SBX_TRY(disc_prepare<T>(c, comp, galaxy, D));
-    double* out = nullptr;
-    const size_t cnt = (size_t)nr * (mmax + 1) * 2;
-    SBX_TRY(D.alloc((void**)&out, sizeof(double) * cnt));
-    hipLaunchKernelGGL(k_disc_modes, dim3(nr), dim3(256), 0, s, D.key, D.order, D.n, D.d3, D.m1, rmax / nr,
-                       mmax, out);
-    SBX_HIP(hipGetLastError());
-    SBX_HIP(hipMemcpyAsync(coeff, out, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));
-    SBX_HIP(hipStreamSynchronize(s));
-    return SBX_OK;
+    SBX_TRY(disc_prepare<T>(c, comp, galaxy, sizeof(double) * (cnt + (size_t)nr * split * width), D));
+    double* out = (double*)D.extra;
+    double* part = out + cnt;
+    const double dR = rmax / nr;
+    return with_order<T>(c, D, out, cnt, coeff, [&]() -> sbx_status {
+      const dim3 g(nr, split), b(256);
+      auto go = [&](auto mc) {
+        hipLaunchKernelGGL((k_disc_modes<T, decltype(mc)::value>), g, b, 0, s, D.key, D.order, D.n, D.rec, D.cen,
+                           dR, D.flag, part);
+      };
+      switch (MM) {
+        case 0: go(std::integral_constant<int, 0>()); break;
+        case 2: go(std::integral_constant<int, 2>()); break;
+        case 4: go(std::integral_constant<int, 4>()); break;
+        case 8: go(std::integral_constant<int, 8>()); break;
+        default: go(std::integral_constant<int, 16>());
+      }
+      hipLaunchKernelGGL(k_disc_modes_end, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, part, split,
+                         (int)width, mmax, nr, dR, out);
+      SBX_HIP(hipGetLastError());
+      return SBX_OK;
+    });
   };
   const sbx_status rc = body();
   (void)hipStreamSynchronize(s);

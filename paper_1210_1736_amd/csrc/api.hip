@@ -290,6 +290,8 @@ void free_particles(sbx_ctx* c) {
   free_typed(c->pot);
   free_ptr(c->adj_work);
   c->adj_work_bytes = 0;
+  free_ptr(c->an_work);
+  c->an_work_bytes = 0;
   c->acc_n = 0;
   c->n = 0;
   c->cur = 0;
