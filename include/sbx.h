@@ -486,7 +486,8 @@ sbx_status sbx_set_fft_schedule(int32_t v);
  * and the odd rows of a plane in two blocks with 256 or 512 threads, or in
  * FP32 also a whole plane with 1024).  form = 0 (the
  * default): the tuner times both the first time a precision, grid size and
- * solve count is planned and keeps the faster.  Like the schedule pin,
+ * solve count is planned and keeps the faster; up to 64 solves with n <= 16
+ * that share no grids run as one launch, a block per solve.  Like the schedule pin,
  * process-wide, for plans made from now on; sizes without the plane form
  * use five passes whatever the pin.  SBX_EINVAL for other values. */
 sbx_status sbx_set_fft_form(int32_t form);

@@ -66,7 +66,7 @@ constexpr int kMaxGroups = 6;  // distinct grid sizes 8..256
 // Solves of one grid size inside a plan.
 struct SolveGroup {
   int first = 0, count = 0, N = 0;
-  int form = 5;                      // 5 line passes, or 3 plane-fused passes
+  int form = 5;                      // 5 line passes, 3 plane-fused passes, or 1 launch (small grids)
   const void* tw[kPasses] = {};      // twiddle table of each pass's lines (2N; N for the plane passes)
   const void* twist = nullptr;       // plane form: exp(-2 pi i n / 2N), n < N
   PassShape shape[kPasses] = {};
@@ -100,8 +100,10 @@ inline size_t h_elems(int N) { return (size_t)(N + 1) * (N + 1) * (N + 1); }
 // Prepare a plan for the given solves (device tables, twiddles, launch
 // shapes from the tuning cache; tunes on the plan's own buffers when the mix
 // of grid sizes is new -- rho/phi/X/C are then overwritten with zeros).
+// small = false leaves the one-launch form out, so that the tuner runs.
 template <typename T>
-sbx_status plan_create(SolvePlan<T>& plan, const SolveDesc<T>* descs, int n, hipStream_t s);
+sbx_status plan_create(SolvePlan<T>& plan, const SolveDesc<T>* descs, int n, hipStream_t s,
+                       bool small = true);
 
 // Run all solves of the plan (five launches per size group; each pass
 // clears the work counter of the pass before it, so the counters are zero
@@ -129,10 +131,11 @@ sbx_status prepare_twiddles(int N, hipStream_t s);
 // The five passes of nsolves solves of N^3 grids whose descriptors are
 // already in device memory, with the tuned launch shapes of (T, N, nsolves)
 // when cached and default shapes otherwise.  Launches only: allocates
-// nothing and waits for nothing (the twiddle table must exist).  d_counter:
-// kPasses work counters, zero on entry, left nonzero.
+// nothing and waits for nothing (the twiddle table must exist).  apart: no
+// solve's masses overlap another's field.  d_counter: kPasses work counters,
+// zero on entry, left nonzero.
 template <typename T>
-sbx_status run_solves_noalloc(const SolveDesc<T>* d_solves, int nsolves, int N, int* d_counter,
+sbx_status run_solves_noalloc(const SolveDesc<T>* d_solves, int nsolves, int N, bool apart, int* d_counter,
                               hipStream_t s);
 
 // Pin the line schedule of plans tuned from now on to v values per thread
@@ -146,8 +149,9 @@ sbx_status set_fft_form(int f);
 // or 0 (time all).  Process-wide.
 sbx_status set_plane_threads(int nt);
 
-// Whether launch shapes for this precision and mix of grid sizes are cached.
-bool tuning_cached(int esz, std::vector<int> mix);
+// Whether a plan of these solves of one grid size needs no tuning run.
+template <typename T>
+bool plan_known(const SolveDesc<T>* descs, int n);
 
 // Tuned launch shapes of every mix planned so far, as text (one line per
 // pass and mix), for reports.

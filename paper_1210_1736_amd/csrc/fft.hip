@@ -1284,6 +1284,125 @@ __global__ void __launch_bounds__(NT)
   }
 }
 
+// ------------------------------------------------------- small grids ---
+// N <= 16: the whole solve in one block and one launch.  The half spectrum,
+// (N+1) x 2N x N complex, stays in LDS at slot (kx, ky, z); rows y < N of a
+// (kx, z) line sit where its frequencies ky will.  A thread transforms a
+// line of 2N in registers (no twiddle tables, no exchanges); the five steps
+// are separated by block barriers.  The z lines, the most, get a thread each
+// (two rounds in FP64, whose 32 complex values need the registers).  What
+// bounds it is the chain of five steps: one 16^3 solve in FP32 took 18.4 us
+// as five launches, whose 18 us of kernels do next to no work.
+template <typename T, int N>
+struct SM {
+  static constexpr int L = 2 * N, PZ = N + 1;
+  static constexpr int LDS = (N + 1) * L * PZ;
+};
+template <typename T>
+constexpr int small_threads(int N) {
+  return N == 8 ? 192 : (sizeof(T) == 4 ? 576 : 320);
+}
+
+template <typename T, int N, int NT>
+__global__ void __launch_bounds__(NT) k_small(const SolveDesc<T>* __restrict__ solves) {
+  using G = SM<T, N>;
+  constexpr int L = G::L, PZ = G::PZ;
+  __shared__ C2<T> s[G::LDS];
+  const SolveDesc<T>& d = solves[blockIdx.x];
+  const int tid = threadIdx.x;
+  auto at = [&](int kx, int k, int z) -> C2<T>& { return s[(kx * L + k) * PZ + z]; };
+  // x: rows 2j and 2j + 1 of plane z as one complex line
+  for (int i = tid; i < N * N / 2; i += NT) {
+    const int z = i % N, j = i / N;
+    const gp<const T> a = glb(d.rho + ((size_t)z * N + 2 * j) * N), b = a + N;
+    C2<T> v[L];
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] = C2<T>{a[n], b[n]};
+    if (d.rho2) {  // summed grids: the second source is added on the way in
+      const gp<const T> a2 = glb(d.rho2 + ((size_t)z * N + 2 * j) * N), b2 = a2 + N;
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        v[n].re += a2[n];
+        v[n].im += b2[n];
+      }
+    }
+#pragma unroll
+    for (int n = N; n < L; ++n) v[n] = C2<T>{(T)0, (T)0};
+    dftR<L, false>(v);
+    const T h = (T)0.5;
+#pragma unroll
+    for (int e = 0; e <= N; ++e) {
+      const C2<T> Z = v[e], R = v[e == 0 ? 0 : L - e];
+      at(e, 2 * j, z) = C2<T>{(Z.re + R.re) * h, (Z.im - R.im) * h};
+      at(e, 2 * j + 1, z) = C2<T>{(Z.im + R.im) * h, (R.re - Z.re) * h};
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < (N + 1) * N; i += NT) {  // y
+    const int z = i % N, kx = i / N;
+    C2<T> v[L];
+#pragma unroll
+    for (int n = 0; n < L; ++n) v[n] = n < N ? at(kx, n, z) : C2<T>{(T)0, (T)0};
+    dftR<L, false>(v);
+#pragma unroll
+    for (int n = 0; n < L; ++n) at(kx, n, z) = v[n];
+  }
+  __syncthreads();
+  for (int i = tid; i < (N + 1) * L; i += NT) {  // z, times Hhat, and back
+    const int ky = i % L, kx = i / L;
+    const gp<const T> H = glb(d.H + ((size_t)kx * (N + 1) + (ky <= N ? ky : L - ky)) * (N + 1));
+    T h[N + 1];
+#pragma unroll
+    for (int e = 0; e <= N; ++e) h[e] = H[e];
+    C2<T> v[L];
+#pragma unroll
+    for (int n = 0; n < L; ++n) v[n] = n < N ? at(kx, ky, n) : C2<T>{(T)0, (T)0};
+    dftR<L, false>(v);
+#pragma unroll
+    for (int e = 0; e < L; ++e) v[e] = cscale(v[e], h[e <= N ? e : L - e]);
+    dftR<L, true>(v);
+#pragma unroll
+    for (int n = 0; n < N; ++n) at(kx, ky, n) = v[n];
+  }
+  __syncthreads();
+  for (int i = tid; i < (N + 1) * N; i += NT) {  // inverse y
+    const int z = i % N, kx = i / N;
+    C2<T> v[L];
+#pragma unroll
+    for (int n = 0; n < L; ++n) v[n] = at(kx, n, z);
+    dftR<L, true>(v);
+#pragma unroll
+    for (int n = 0; n < N; ++n) at(kx, n, z) = v[n];
+  }
+  __syncthreads();
+  for (int i = tid; i < N * N / 2; i += NT) {  // inverse x of two rows: A + iB
+    const int z = i % N, j = i / N;
+    C2<T> v[L];
+#pragma unroll
+    for (int e = 0; e <= N; ++e) {
+      const C2<T> a = at(e, 2 * j, z), q = at(e, 2 * j + 1, z);
+      v[e] = C2<T>{a.re - q.im, a.im + q.re};
+      if (e > 0 && e < N) v[L - e] = C2<T>{a.re + q.im, q.re - a.im};
+    }
+    dftR<L, true>(v);
+    const gp<T> da = glb(d.phi + ((size_t)z * N + 2 * j) * N), db = da + N;
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      da[n] = v[n].re;
+      db[n] = v[n].im;
+    }
+  }
+}
+
+template <typename T>
+static void launch_small(const SolveDesc<T>* solves, int N, int nsolves, hipStream_t st) {
+  constexpr int n8 = small_threads<T>(8), n16 = small_threads<T>(16);
+  if (N == 8)
+    hipLaunchKernelGGL((k_small<T, 8, n8>), dim3(nsolves), dim3(n8), 0, st, solves);
+  else
+    hipLaunchKernelGGL((k_small<T, 16, n16>), dim3(nsolves), dim3(n16), 0, st, solves);
+}
+
 template <typename T, int L, int V, int NT, int PASS>
 __device__ __forceinline__ void run_tile(const SolveDesc<T>& d, int tile, C2<T>* s,
                                          const C2<T>* __restrict__ tw) {
@@ -1644,25 +1763,46 @@ static int device_cus() {
   return cus > 0 ? cus : 256;
 }
 
-bool tuning_cached(int esz, std::vector<int> mix) {
-  std::sort(mix.begin(), mix.end());
-  for (size_t i = 0; i < mix.size();) {
-    size_t j = i;
-    while (j < mix.size() && mix[j] == mix[i]) ++j;
-    Tuned a;
-    if (!tune_lookup(key_now(esz, mix[i], (int)(j - i)), a)) return false;
-    i = j;
+// Form 1 wherever a solve fits one block, unless a form is pinned.  Against
+// the five launches, for 1 and for 40 solves a call: 3.9 and 3.9 us against
+// 18.2 and 18.4 (16^3 FP32), 5.0 and 5.1 against 18.4 and 18.9 (16^3 FP64),
+// 3.9 against 18.3 (8^3).
+constexpr int kSmallCount = 64;
+static bool small_form(int N, int count) { return N <= 16 && count <= kSmallCount && g_pin_form.load() == 0; }
+
+// In form 1 a solve writes its field while others still read their masses:
+// no solve may read what another one writes (the summed grids of a galaxy
+// do).
+template <typename T>
+static bool solves_disjoint(const SolveDesc<T>* d, int n) {
+  for (int i = 0; i < n; ++i) {
+    if (d[i].rho2) return false;
+    const size_t cells = (size_t)d[i].N * d[i].N * d[i].N;
+    for (int j = 0; j < n; ++j)
+      if (j != i && d[i].rho < d[j].phi + cells && (const T*)d[j].phi < d[i].rho + cells) return false;
   }
   return true;
 }
 
-// One pass of a group in either form.  Plane form: pass 0 is the plane
-// forward, 2 the z pass on the plane layout, 3 the plane inverse; 1 and 4
+template <typename T>
+bool plan_known(const SolveDesc<T>* d, int n) {
+  if (n <= 0) return true;
+  if (small_form(d[0].N, n) && solves_disjoint<T>(d, n)) return true;
+  Tuned a;
+  return tune_lookup(key_now((int)sizeof(T), d[0].N, n), a);
+}
+template bool plan_known<float>(const SolveDesc<float>*, int);
+template bool plan_known<double>(const SolveDesc<double>*, int);
+
+// One pass of a group in any form.  Form 1: one launch, as pass 2.  Plane
+// form: pass 0 is the plane forward, 2 the z pass on the plane layout, 3 the plane inverse; 1 and 4
 // launch nothing.  Each launch clears the work counter of the pass before.
 template <typename T>
 static void run_pass(int form, int q, const SolveDesc<T>* solves, int N, int count, const PassShape& sh,
                      int* ctr, int* prev, const C2<T>* tw, const C2<T>* twist, hipStream_t st) {
-  if (form != 3) {
+  if (form == 1) {
+    if (q == 2) launch_small<T>(solves, N, count, st);
+  } else if (form != 3) {
     launch_any<T>(q, solves, N, count, sh, ctr, prev, tw, st);
   } else if (q == 0 || q == 3) {
     launch_plane<T>(q == 3, solves, N, count, sh.nt, prev, tw, twist, st);
@@ -1837,7 +1977,7 @@ static sbx_status tune_group(const SolveDesc<T>* d_solves, const SolveDesc<T>* h
 }
 
 template <typename T>
-sbx_status plan_create(SolvePlan<T>& p, const SolveDesc<T>* descs, int n, hipStream_t st) {
+sbx_status plan_create(SolvePlan<T>& p, const SolveDesc<T>* descs, int n, hipStream_t st, bool small) {
   plan_destroy(p);
   if (n <= 0) return SBX_OK;
   for (int i = 0; i < n; ++i) {
@@ -1890,7 +2030,9 @@ sbx_status plan_create(SolvePlan<T>& p, const SolveDesc<T>* descs, int n, hipStr
     SolveGroup& g = p.groups[gi];
     Tuned a;
     const TuneKey key = key_now((int)sizeof(T), g.N, g.count);
-    if (!tune_lookup(key, a)) {
+    if (small && small_form(g.N, g.count) && solves_disjoint<T>(p.host.data() + g.first, g.count)) {
+      a.form = 1;
+    } else if (!tune_lookup(key, a)) {
       SBX_TRY(tune_group<T>(p.d_solves + g.first, p.host.data() + g.first, g.N, g.count,
                             p.d_counter, st, a));
       std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1904,7 +2046,7 @@ sbx_status plan_create(SolvePlan<T>& p, const SolveDesc<T>* descs, int n, hipStr
     for (int q = 0; q < kPasses; ++q) {
       g.shape[q] = a.sh[q];
       g.tw[q] = nullptr;
-      if (g.form == 3 && (q == 1 || q == 4)) continue;
+      if (g.form == 1 || (g.form == 3 && (q == 1 || q == 4))) continue;
       // the plane passes transform lines of N (16 values per lane)
       const bool pq = g.form == 3 && q != 2;
       const C2<T>* tw = pq ? twiddles<T>(g.N, 16, st) : twiddles<T>(2 * g.N, a.sh[q].v, st);
@@ -1978,9 +2120,14 @@ sbx_status prepare_twiddles(int N, hipStream_t st) {
 }
 
 template <typename T>
-sbx_status run_solves_noalloc(const SolveDesc<T>* d_solves, int nsolves, int N, int* d_counter,
+sbx_status run_solves_noalloc(const SolveDesc<T>* d_solves, int nsolves, int N, bool apart, int* d_counter,
                               hipStream_t st) {
   Tuned a;
+  if (apart && small_form(N, nsolves)) {
+    launch_small<T>(d_solves, N, nsolves, st);
+    SBX_HIP(hipGetLastError());
+    return SBX_OK;
+  }
   if (!tune_lookup(key_now((int)sizeof(T), N, nsolves), a))
     for (auto& sh : a.sh) sh = PassShape{256, 0, 0};
   const C2<T>* tw[kPasses] = {};
@@ -2006,8 +2153,8 @@ sbx_status run_solves_noalloc(const SolveDesc<T>* d_solves, int nsolves, int N, 
 
 template sbx_status prepare_twiddles<float>(int, hipStream_t);
 template sbx_status prepare_twiddles<double>(int, hipStream_t);
-template sbx_status run_solves_noalloc<float>(const SolveDesc<float>*, int, int, int*, hipStream_t);
-template sbx_status run_solves_noalloc<double>(const SolveDesc<double>*, int, int, int*, hipStream_t);
+template sbx_status run_solves_noalloc<float>(const SolveDesc<float>*, int, int, bool, int*, hipStream_t);
+template sbx_status run_solves_noalloc<double>(const SolveDesc<double>*, int, int, bool, int*, hipStream_t);
 
 template <typename T>
 void plan_destroy(SolvePlan<T>& p) {
@@ -2021,8 +2168,8 @@ void plan_destroy(SolvePlan<T>& p) {
   p = SolvePlan<T>();
 }
 
-template sbx_status plan_create<float>(SolvePlan<float>&, const SolveDesc<float>*, int, hipStream_t);
-template sbx_status plan_create<double>(SolvePlan<double>&, const SolveDesc<double>*, int, hipStream_t);
+template sbx_status plan_create<float>(SolvePlan<float>&, const SolveDesc<float>*, int, hipStream_t, bool);
+template sbx_status plan_create<double>(SolvePlan<double>&, const SolveDesc<double>*, int, hipStream_t, bool);
 template sbx_status plan_run<float>(const SolvePlan<float>&, hipStream_t, Recorder*);
 template sbx_status plan_run<double>(const SolvePlan<double>&, hipStream_t, Recorder*);
 template sbx_status plan_run_pass<float>(const SolvePlan<float>&, int, int, hipStream_t);

@@ -159,13 +159,13 @@ sbx_status poisson_solve_t(sbx_poisson* p, int batch, const void* rho, void* phi
         }
         return d;
       };
-      if (!tuning_cached((int)sizeof(T), std::vector<int>(nb, p->N))) {
+      if (!plan_known<T>(descs((const T*)r, (T*)f).data(), nb)) {
         // tune on scratch grids, never on the caller's buffers
         T* scratch = nullptr;
         SBX_TRY(dev_alloc((void**)&scratch, sizeof(T) * cells * nb));
         SolvePlan<T> tmp;
         auto d = descs(scratch, scratch);
-        const sbx_status rc = plan_create<T>(tmp, d.data(), nb, p->stream);
+        const sbx_status rc = plan_create<T>(tmp, d.data(), nb, p->stream, false);
         plan_destroy(tmp);
         (void)hipFree(scratch);
         SBX_TRY(rc);
@@ -297,7 +297,9 @@ sbx_status poisson_noalloc_t(sbx_poisson* p, int batch, const void* rho, void* p
                      (T*)phi, (C2<T>*)(s + off_x), (C2<T>*)(s + off_cd), (const T*)p->H, N, cells, xe,
                      ce, counters, kPasses);
   SBX_HIP(hipGetLastError());
-  return run_solves_noalloc<T>(d, batch, N, counters, p->stream);
+  const T *r0 = (const T*)rho, *f0 = (const T*)phi;
+  const bool apart = r0 == f0 || r0 + cells * batch <= f0 || f0 + cells * batch <= r0;
+  return run_solves_noalloc<T>(d, batch, N, apart, counters, p->stream);
 }
 
 }  // namespace
