@@ -94,7 +94,7 @@ struct InstDev {
   double* pre_partial;      // kPreVals columns of kRedBlocks block rows (column-major)
   double* diag_partial;     // force_blocks(n) rows of kNDiag
   double* diag_out;         // kNDiag: where the next diagnostics record goes
-  double* acc;              // n * 3 (write mode)
+  double* acc;              // n * 3 (write mode, caller's order, as pot)
   double* pot;              // n (write mode, physical potential)
   T* grid_block;            // all grids of the instance, back to back
   size_t grid_elems;        // the leading grids that take masses (cleared per step)

@@ -995,10 +995,13 @@ __global__ void __launch_bounds__(256)
     double dv[DIAG ? kDiagComp : 1];    // this lane's contribution
     int cg = -1;                        // galaxy for the centre-of-mass sums
     double cm = 0.0, cx = 0.0, cy = 0.0, cz = 0.0;
+    // accelerations and potentials go out in the caller's order
+    [[maybe_unused]] int64_t j = 0;
+    if constexpr (OUT) j = valid ? glb((const int32_t*)p.id)[i] : 0;
     if (valid && !live) {
       if constexpr (OUT) {
-        I.acc[3 * i] = I.acc[3 * i + 1] = I.acc[3 * i + 2] = 0.0;
-        I.pot[i] = 0.0;
+        I.acc[3 * j] = I.acc[3 * j + 1] = I.acc[3 * j + 2] = 0.0;
+        I.pot[j] = 0.0;
       }
       if constexpr (DIAG) dd[5] += 1.0;
     }
@@ -1023,10 +1026,10 @@ __global__ void __launch_bounds__(256)
       else
         particle_field<false>(sys, centres, F, x, y, z, a, phi, OUT || DIAG);
       if constexpr (OUT) {
-        I.acc[3 * i] = (double)a[0];
-        I.acc[3 * i + 1] = (double)a[1];
-        I.acc[3 * i + 2] = (double)a[2];
-        I.pot[i] = -(double)phi;
+        I.acc[3 * j] = (double)a[0];
+        I.acc[3 * j + 1] = (double)a[1];
+        I.acc[3 * j + 2] = (double)a[2];
+        I.pot[j] = -(double)phi;
       }
       if constexpr (DIAG) {
         const double m = (double)mi;

@@ -44,3 +44,27 @@ def test_readback_in_callers_order(sbx, prec, n):
     ctx.sbx_step(0.0, 1)  # the staging left the live set alone
     assert np.array_equal(ctx.sbx_get_particles()[0], x)
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n", [1, 300, 40001])
+def test_forces_in_callers_order(sbx, prec, n):
+    """Accelerations and potentials of a reordered context against the same
+    context before the reorder: the same particles at the same rows, to the
+    rounding of the cell sums (as the float and fixed-point assignments
+    agree: 1e-10 FP64, 1e-4 FP32 of the rms); lost particles zero."""
+    rng = np.random.default_rng(np.random.SeedSequence([1210, 1736, 986, n]))
+    x = rng.uniform(-1.05, 1.05, (n, 3))
+    x[0] = 0.1
+    ctx = sbx.Context(prec=prec)
+    ctx.sbx_build_grids([sbx.make_hierarchy([(16, 1.0, 1.0)])])
+    ctx.sbx_load_particles(x, np.zeros_like(x), np.full(n, 1.0 / n), np.zeros(n, np.int8), np.zeros(n, np.int8))
+    a0, p0 = ctx.sbx_compute_forces()
+    ctx.sbx_step(0.0, 1)
+    a1, p1 = ctx.sbx_compute_forces()
+    lost = ctx.sbx_get_particles()[2]
+    tol = 1e-10 if prec == sbx.SBX_FP64 else 1e-4
+    scale = max(np.sqrt(np.mean(a0 * a0)), np.abs(p0).max() * 1e-3)
+    assert np.abs(a1 - a0).max() <= tol * scale and np.abs(p1 - p0).max() <= tol * np.abs(p0).max()
+    assert not a1[lost].any() and not p1[lost].any() and (p1[~lost] < 0).all()
+    ctx.close()
