@@ -228,9 +228,10 @@ sbx_status sbx_diagnostics(sbx_ctx* ctx, double dt, sbx_diag* out);
 sbx_status sbx_diag_log(sbx_ctx* ctx, int32_t max, sbx_diag* out, int32_t* count);
 
 /* Differentiable segment: nsteps integration cycles from the current state
- * (no reordering inside), then the reverse mode of the discrete cycles, with
- * (x, v) checkpoints every ckpt_every steps and the positions between
- * checkpoints recomputed.  Loss L = sum over the live particles of component
+ * (no reordering inside), then the reverse mode of the discrete cycles.  The
+ * last cycles' positions and fields are kept from the forward (those of the
+ * last ckpt_every cycles, and of more where 4 GiB hold them); the others are
+ * recomputed from (x, v) checkpoints every ckpt_every steps.  Loss L = sum over the live particles of component
  * sel_comp of galaxy sel_gal of 1/2 m v_z^2, with v the staggered velocity
  * after the last kick.  Outputs (host, caller's particle order, any may be
  * NULL): loss (1), grad_m = dL/dm (n), grad_x = dL/dx (n*3) and

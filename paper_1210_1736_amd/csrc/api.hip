@@ -424,9 +424,9 @@ const InstDev<T>* dinst(sbx_ctx* c) {
   return (const InstDev<T>*)c->d_inst;
 }
 
-// Loss test, centres, mass assignment and all isolated solves of one step.
+// Loss test, centres and mass assignment of one step.
 template <typename T>
-sbx_status field_solve_t(sbx_ctx* c) {
+sbx_status deposit_t(sbx_ctx* c) {
   const std::vector<InstInfo> info{info_of(c)};
   c->rec.mark(PH_START, c->stream);
   if (c->com_fresh && c->dm_elems == 0) {
@@ -439,6 +439,13 @@ sbx_status field_solve_t(sbx_ctx* c) {
   c->rec.mark(PH_PRE, c->stream);
   SBX_TRY(launch_deposit<T>(dinst<T>(c), c->d_cur, info, c->stream));
   c->rec.mark(PH_DEPOSIT, c->stream);
+  return SBX_OK;
+}
+
+// The same and all isolated solves.
+template <typename T>
+sbx_status field_solve_t(sbx_ctx* c) {
+  SBX_TRY(deposit_t<T>(c));
   if constexpr (sizeof(T) == 8) SBX_TRY(plan_run<T>(c->plan64, c->stream, &c->rec));
   else SBX_TRY(plan_run<T>(c->plan32, c->stream, &c->rec));
   c->solved = true;
@@ -593,10 +600,16 @@ sbx_status ensure_sort_arrays(sbx_ctx* c) {
   return upload_inst(c);
 }
 
-// Forward nsteps without sorting, checkpoints of (x, v, lost) every
-// ckpt_every steps, then the reverse cycles interval by interval.  The
-// positions, lost flags and fields of an interval's cycles are recomputed
-// from its checkpoint (the last interval keeps them from the forward pass):
+// Records the forward of a segment may keep beyond its last interval.
+constexpr size_t kKeepBytes = (size_t)4 << 30;
+
+// Forward nsteps without sorting, then the reverse cycles interval by
+// interval.  The positions, lost flags and fields of the last intervals'
+// cycles are kept from the forward pass, as many intervals as kKeepBytes
+// hold besides the last one; those of the others are recomputed from
+// checkpoints of (x, v, lost) every ckpt_every steps (with the records of
+// all three intervals kept, a six-cycle segment on a 256^3 grid runs 12
+// solves instead of 16):
 // each cycle's solve runs from the particles that take part in it (live
 // after its start-of-step loss test), and its lost flags and fields are kept
 // for the reverse cycle, which scatters the adjoint sources, solves them and
@@ -616,22 +629,47 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   SBX_TRY(set_dt(c, dt));
   const int64_t n = c->n;
   const int nck = (nsteps + ckpt - 1) / ckpt;
-  // carve the work buffer: checkpoints (x, v, lost), per-cycle (x, lost) and
-  // fields of one interval, adjoint state, loss, staging
-  size_t need = 0;
-  auto take = [&](size_t bytes) { const size_t at = need; need += (bytes + 255) & ~(size_t)255; return at; };
-  std::vector<size_t> ck_off(nck + 1), xb_off(ckpt), fb_off(ckpt);
   const size_t pitch = row_pitch(n, sizeof(T)), set_x = 3 * pitch;
-  for (auto& o : ck_off) o = take(2 * set_x + n);
-  for (auto& o : xb_off) o = take(set_x + n);
-  for (auto& o : fb_off) o = take(sizeof(T) * c->grid_elems);
-  const size_t lx_off = take(sizeof(double) * 3 * n), lv_off = take(sizeof(double) * 3 * n);
-  const size_t gm_off = take(sizeof(double) * n), dl_off = take(sizeof(double) * 4);
-  const size_t st_off = take(sizeof(double) * 3 * n);
+  const size_t gbytes = sizeof(T) * c->grid_elems;
+  SolvePlan<T>& fwd = sizeof(T) == 8 ? (SolvePlan<T>&)c->plan64 : (SolvePlan<T>&)c->plan32;
+  // intervals whose records the forward keeps: the last one, and the ones
+  // before it as far as kKeepBytes go
+  const size_t rec_bytes = set_x + n + gbytes;
+  int kept = (int)std::min<size_t>(nck, 1 + kKeepBytes / (rec_bytes * ckpt));
+  // carve the work buffer: checkpoints (x, v, lost) of the intervals that are
+  // recomputed and the final state, records (x, lost, fields), their solve
+  // descriptors and instance records, adjoint state, loss, staging
+  size_t need, lx_off, lv_off, gm_off, dl_off, st_off, sd_off, in_off;
+  std::vector<size_t> ck_off, xb_off, fb_off;
+  auto carve = [&]() {
+    need = 0;
+    auto take = [&](size_t bytes) { const size_t at = need; need += (bytes + 255) & ~(size_t)255; return at; };
+    const int slots = std::min(kept * ckpt, nsteps);
+    ck_off.resize(kept < nck ? nck - kept + 1 : 0);
+    xb_off.resize(slots);
+    fb_off.resize(slots);
+    for (auto& o : ck_off) o = take(2 * set_x + n);
+    for (auto& o : xb_off) o = take(set_x + n);
+    for (auto& o : fb_off) o = take(gbytes);
+    sd_off = take(sizeof(SolveDesc<T>) * fwd.nsolves * slots);
+    in_off = take(sizeof(InstDev<T>) * slots);
+    lx_off = take(sizeof(double) * 3 * n);
+    lv_off = take(sizeof(double) * 3 * n);
+    gm_off = take(sizeof(double) * n);
+    dl_off = take(sizeof(double) * 4);
+    st_off = take(sizeof(double) * 3 * n);
+  };
+  carve();
   if (c->adj_work_bytes < need) {
     free_ptr(c->adj_work);
     c->adj_work_bytes = 0;
-    SBX_TRY(dev_alloc(&c->adj_work, need));
+    sbx_status rc = dev_alloc(&c->adj_work, need);
+    if (rc == SBX_ENOMEM && kept > 1) {  // the last interval only
+      kept = 1;
+      carve();
+      rc = dev_alloc(&c->adj_work, need);
+    }
+    SBX_TRY(rc);
     c->adj_work_bytes = need;
   }
   char* base = (char*)c->adj_work;
@@ -645,15 +683,14 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     }
     s.lost = (uint8_t*)q;
   };
-  std::vector<PSet> cks(nck + 1), xb(ckpt);
-  for (int i = 0; i <= nck; ++i) set_at(ck_off[i], true, cks[i]);
-  for (int i = 0; i < ckpt; ++i) set_at(xb_off[i], false, xb[i]);
+  std::vector<PSet> cks(ck_off.size()), xb(xb_off.size());
+  for (size_t i = 0; i < cks.size(); ++i) set_at(ck_off[i], true, cks[i]);
+  for (size_t i = 0; i < xb.size(); ++i) set_at(xb_off[i], false, xb[i]);
   double* lx = (double*)(base + lx_off);
   double* lv = (double*)(base + lv_off);
   double* gm = (double*)(base + gm_off);
   double* dloss = (double*)(base + dl_off);
   double* stage = (double*)(base + st_off);
-  const size_t gbytes = sizeof(T) * c->grid_elems;
   // reorder by cell once for the segment (locality of the gathers and of
   // the adjoint scatter); nothing is reordered inside the segment
   bool sort = c->sort_every > 0;
@@ -664,35 +701,61 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   }
   if (sort) SBX_TRY(sort_particles(c));
   PSet& live = c->set[c->cur];
+  // A record's fields are solved straight into it: each record has the
+  // forward solves with their outputs there, and an instance whose fields
+  // are there for the force pass and the reverse cycle to read.
+  InstDev<T>* const rinst = (InstDev<T>*)(base + in_off);
+  SolveDesc<T>* const rdesc = (SolveDesc<T>*)(base + sd_off);
+  std::vector<SolveDesc<T>> hdesc;
+  std::vector<InstDev<T>> hinst(xb.size(), inst_of<T>(c));
+  for (size_t r = 0; r < xb.size(); ++r) {
+    T* const f = (T*)(base + fb_off[r]);
+    for (auto e : fwd.host) {
+      e.phi = f + (e.phi - (T*)c->grid_block);
+      hdesc.push_back(e);
+    }
+    for (int g = 0; g < c->ngal; ++g)
+      for (int k = 0; k < c->nslots[g]; ++k) hinst[r].G.g[g][k] = f + ((T*)c->grid[g][k] - (T*)c->grid_block);
+  }
+  SBX_HIP(hipMemcpyAsync(rdesc, hdesc.data(), sizeof(SolveDesc<T>) * hdesc.size(), hipMemcpyHostToDevice,
+                         c->stream));
+  SBX_HIP(hipMemcpyAsync(rinst, hinst.data(), sizeof(InstDev<T>) * hinst.size(), hipMemcpyHostToDevice,
+                         c->stream));
   // one cycle with its record for the reverse: positions before the solve,
   // lost flags after its loss test, fields after the solve
   auto cycle = [&](int slot, bool move) -> sbx_status {
     SBX_TRY(copy_set<T>(c, xb[slot], live, false, false));
-    SBX_TRY(field_solve(c));
+    SBX_TRY(deposit_t<T>(c));
     SBX_HIP(hipMemcpyAsync(xb[slot].lost, live.lost, n, hipMemcpyDeviceToDevice, c->stream));
-    SBX_HIP(hipMemcpyAsync(base + fb_off[slot], c->grid_block, gbytes, hipMemcpyDeviceToDevice, c->stream));
-    if (move) SBX_TRY(force(c, 1));
+    SBX_TRY(plan_run<T>(fwd, c->stream, nullptr, rdesc + (size_t)fwd.nsolves * slot));
+    c->solved = true;
+    if (!move) return SBX_OK;
+    const std::vector<InstInfo> info{info_of(c)};
+    SBX_TRY(launch_force<T>(rinst + slot, c->d_cur, info, 1, c->stream));
+    c->com_fresh = true;
     return SBX_OK;
   };
-  // forward with checkpoints; the last interval keeps its records
-  const int k0_last = (nck - 1) * ckpt;
+  // forward; the kept intervals leave their records, the others a checkpoint
+  const int k0_kept = (nck - kept) * ckpt;
   for (int k = 0; k < nsteps; ++k) {
-    if (k % ckpt == 0) SBX_TRY(copy_set<T>(c, cks[k / ckpt], live, true, true));
-    if (k >= k0_last) {
-      SBX_TRY(cycle(k - k0_last, true));
+    if (k >= k0_kept) {
+      SBX_TRY(cycle(k - k0_kept, true));
     } else {
+      if (k % ckpt == 0) SBX_TRY(copy_set<T>(c, cks[k / ckpt], live, true, true));
       SBX_TRY(field_solve(c));
       SBX_TRY(force(c, 1));
     }
   }
-  if (nck > 1) SBX_TRY(copy_set<T>(c, cks[nck], live, true, true));  // final state
+  if (kept < nck) SBX_TRY(copy_set<T>(c, cks.back(), live, true, true));  // final state
   SBX_TRY(launch_adj_init<T>(dinst<T>(c), c->d_cur, n, sel_comp, sel_gal, lx, lv, gm, c->pre_partial,
                              dloss, c->stream));
   const GridsDev<T> B = adj_grids<T>(c);
   SolvePlan<T>& adj = sizeof(T) == 8 ? (SolvePlan<T>&)c->adj64 : (SolvePlan<T>&)c->adj32;
   for (int seg = nck - 1; seg >= 0; --seg) {
     const int k0 = seg * ckpt, k1 = std::min(k0 + ckpt, nsteps);
-    if (seg < nck - 1) {
+    const bool again = seg < nck - kept;
+    const int s0 = again ? 0 : k0 - k0_kept;  // the interval's first record
+    if (again) {
       SBX_TRY(copy_set<T>(c, live, cks[seg], true, true));
       c->com_fresh = false;  // the first solve runs the start-of-step loss test
       for (int k = k0; k < k1; ++k) SBX_TRY(cycle(k - k0, k + 1 < k1));
@@ -700,17 +763,17 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     for (int k = k1 - 1; k >= k0; --k) {
       // positions, sat-out flags and forward fields of cycle k, read from
       // where they were kept
+      const int r = s0 + k - k0;
       AdjCycle<T> at;
-      for (int q = 0; q < 3; ++q) at.x[q] = (const T*)xb[k - k0].x[q];
-      at.out = xb[k - k0].lost;
-      at.fields = (const T*)(base + fb_off[k - k0]) - (const T*)c->grid_block;
+      for (int q = 0; q < 3; ++q) at.x[q] = (const T*)xb[r].x[q];
+      at.out = xb[r].lost;
       SBX_TRY(launch_zero<T>((T*)c->adj_block, c->grid_elems, c->stream));
-      SBX_TRY(launch_adj_step<T>(dinst<T>(c), n, at, B, lx, lv, c->stream));
+      SBX_TRY(launch_adj_step<T>(rinst + r, n, at, B, lx, lv, c->stream));
       SBX_TRY(plan_run<T>(adj, c->stream));
       SBX_TRY(launch_adj_gather<T>(dinst<T>(c), c->d_cur, n, at, B, gm, c->stream));
     }
   }
-  if (nck > 1) SBX_TRY(copy_set<T>(c, live, cks[nck], true, true));  // back to the final state
+  if (kept < nck) SBX_TRY(copy_set<T>(c, live, cks.back(), true, true));  // back to the final state
   if (c->bound && c->cur == 1)
     SBX_TRY(launch_state_home<T>(pset_dev<T>(live, n), pset_dev<T>(c->set[0], n), c->stream));
   c->com_fresh = false;

@@ -109,16 +109,19 @@ sbx_status plan_create(SolvePlan<T>& plan, const SolveDesc<T>* descs, int n, hip
 // clears the work counter of the pass before it, so the counters are zero
 // between runs).  With several size groups the groups run on concurrent
 // streams between a fork and a join on s; phase marks are then all taken
-// at the join.
+// at the join.  solves: other descriptors on the device in the place of the
+// plan's own (as many, in its order, on its work arrays), or null.
 template <typename T>
-sbx_status plan_run(const SolvePlan<T>& plan, hipStream_t s, Recorder* rec = nullptr);
+sbx_status plan_run(const SolvePlan<T>& plan, hipStream_t s, Recorder* rec = nullptr,
+                    const SolveDesc<T>* solves = nullptr);
 
 // One pass (0..4) of one size group, for callers that schedule the groups
 // themselves (e.g. as concurrent branches of a graph).  Clears the work
 // counter of the previous pass of the group: run the passes of a group in
 // order 0..4, each after the one before it has finished.
 template <typename T>
-sbx_status plan_run_pass(const SolvePlan<T>& plan, int pass, int group, hipStream_t s);
+sbx_status plan_run_pass(const SolvePlan<T>& plan, int pass, int group, hipStream_t s,
+                         const SolveDesc<T>* solves = nullptr);
 
 template <typename T>
 void plan_destroy(SolvePlan<T>& plan);

@@ -2088,23 +2088,23 @@ sbx_status plan_create(SolvePlan<T>& p, const SolveDesc<T>* descs, int n, hipStr
 }
 
 template <typename T>
-sbx_status plan_run_pass(const SolvePlan<T>& p, int q, int group, hipStream_t st) {
+sbx_status plan_run_pass(const SolvePlan<T>& p, int q, int group, hipStream_t st, const SolveDesc<T>* solves) {
   const SolveGroup& g = p.groups[group];
-  run_pass<T>(g.form, q, p.d_solves + g.first, g.N, g.count, g.shape[q], p.d_counter + q * kMaxGroups + group,
+  run_pass<T>(g.form, q, (solves ? solves : p.d_solves) + g.first, g.N, g.count, g.shape[q], p.d_counter + q * kMaxGroups + group,
               p.d_counter + ((q + kPasses - 1) % kPasses) * kMaxGroups + group, (const C2<T>*)g.tw[q],
               (const C2<T>*)g.twist, st);
   return SBX_OK;
 }
 
 template <typename T>
-sbx_status plan_run(const SolvePlan<T>& p, hipStream_t st, Recorder* rec) {
+sbx_status plan_run(const SolvePlan<T>& p, hipStream_t st, Recorder* rec, const SolveDesc<T>* solves) {
   if (p.nsolves == 0) return SBX_OK;
   Recorder none;
   Recorder& r = rec ? *rec : none;
   static const int marks[kPasses] = {PH_FWD_X, PH_FWD_Y, PH_ZPASS, PH_INV_Y, PH_INV_X};
   if (p.ngroups == 1) {
     for (int q = 0; q < kPasses; ++q) {
-      SBX_TRY(plan_run_pass<T>(p, q, 0, st));
+      SBX_TRY(plan_run_pass<T>(p, q, 0, st, solves));
       r.mark(marks[q], st);
     }
   } else {
@@ -2113,7 +2113,7 @@ sbx_status plan_run(const SolvePlan<T>& p, hipStream_t st, Recorder* rec) {
     SBX_HIP(hipEventRecord(p.fork, st));
     for (int gi = 1; gi < p.ngroups; ++gi) SBX_HIP(hipStreamWaitEvent(p.side[gi], p.fork, 0));
     for (int gi = 0; gi < p.ngroups; ++gi)
-      for (int q = 0; q < kPasses; ++q) SBX_TRY(plan_run_pass<T>(p, q, gi, gi == 0 ? st : p.side[gi]));
+      for (int q = 0; q < kPasses; ++q) SBX_TRY(plan_run_pass<T>(p, q, gi, gi == 0 ? st : p.side[gi], solves));
     for (int gi = 1; gi < p.ngroups; ++gi) {
       SBX_HIP(hipEventRecord(p.join[gi], p.side[gi]));
       SBX_HIP(hipStreamWaitEvent(st, p.join[gi], 0));
@@ -2189,10 +2189,10 @@ void plan_destroy(SolvePlan<T>& p) {
 
 template sbx_status plan_create<float>(SolvePlan<float>&, const SolveDesc<float>*, int, hipStream_t, bool);
 template sbx_status plan_create<double>(SolvePlan<double>&, const SolveDesc<double>*, int, hipStream_t, bool);
-template sbx_status plan_run<float>(const SolvePlan<float>&, hipStream_t, Recorder*);
-template sbx_status plan_run<double>(const SolvePlan<double>&, hipStream_t, Recorder*);
-template sbx_status plan_run_pass<float>(const SolvePlan<float>&, int, int, hipStream_t);
-template sbx_status plan_run_pass<double>(const SolvePlan<double>&, int, int, hipStream_t);
+template sbx_status plan_run<float>(const SolvePlan<float>&, hipStream_t, Recorder*, const SolveDesc<float>*);
+template sbx_status plan_run<double>(const SolvePlan<double>&, hipStream_t, Recorder*, const SolveDesc<double>*);
+template sbx_status plan_run_pass<float>(const SolvePlan<float>&, int, int, hipStream_t, const SolveDesc<float>*);
+template sbx_status plan_run_pass<double>(const SolvePlan<double>&, int, int, hipStream_t, const SolveDesc<double>*);
 template void plan_destroy<float>(SolvePlan<float>&);
 template void plan_destroy<double>(SolvePlan<double>&);
 

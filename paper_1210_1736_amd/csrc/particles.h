@@ -211,14 +211,12 @@ template <typename T>
 sbx_status launch_indices(const InstDev<T>* inst, const int* cur, int64_t n, int galaxy, int level,
                           int32_t* idx, int8_t* cls, hipStream_t s);
 
-// What the reverse of one cycle reads of it: positions before the cycle, the
-// flags of the particles that sat it out, and how far (in elements) the kept
-// fields lie from the instance's grid block.
+// What the reverse of one cycle reads of it besides the fields: positions
+// before the cycle and the flags of the particles that sat it out.
 template <typename T>
 struct AdjCycle {
   const T* x[3];
   const uint8_t* out;
-  ptrdiff_t fields;
 };
 
 // Reverse mode of a leapfrog segment (single instance, fixed centres).

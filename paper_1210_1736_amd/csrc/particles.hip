@@ -1501,7 +1501,7 @@ __global__ void __launch_bounds__(256)
       uint32_t key = kNoKey;
       if (slot >= 0) {
         key = dep_key(g, slot, L, cl.idx[lev]);
-        eq8_adjoint_weights(F.g[g][slot] + at.fields, L, cl.idx[lev], outer ? ox : dx, outer ? oy : dy,
+        eq8_adjoint_weights(F.g[g][slot], L, cl.idx[lev], outer ? ox : dx, outer ? oy : dy,
                             outer ? oz : dz, sys.taylor, mu, l, w);
       } else {
 #pragma unroll

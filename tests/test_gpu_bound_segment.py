@@ -65,3 +65,28 @@ def test_bound_segment(sbx, prec, kind, ckpt, sort):
         xg, _, _ = ctx.sbx_get_particles()
         assert np.array_equal(st[0].double().cpu().numpy().T, xg)
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_records_beyond_the_kept_ones(sbx, prec):
+    """A segment whose records do not all fit in 4 GiB (128^3 cells on three
+    levels, 7 x 2^21 values a record): intervals kept from the forward and
+    intervals recomputed, several of each, against one that keeps every cycle
+    of one interval.  The two run the same cycles and differ by the order of
+    the cell sums: the bars of the segment."""
+    w = _workload("nested", n=4000, seed=5)
+    steps = 80 if prec == sbx.SBX_FP32 else 44  # 58.7 or 117.4 MB a record: 73 or 36 cycles fit
+    out = []
+    for ckpt in (8, steps):
+        ctx = sbx.Context(prec=prec, G=w.G)
+        ctx.sbx_build_grids([sbx.make_hierarchy([(128, l.R, l.q) for l in w.hier[0].levels])])
+        ctx.sbx_load_particles(w.x, w.v, w.m, w.comp, w.gal)
+        out.append((ctx.sbx_adjoint_segment(1e-3, steps, ckpt, 1, 0), ctx.sbx_get_particles()))
+        ctx.close()
+    (la, gma, gxa, gva), sa = out[0]
+    (lb, gmb, gxb, gvb), sb = out[1]
+    f64 = prec == sbx.SBX_FP64
+    assert la == pytest.approx(lb, rel=1e-12 if f64 else 1e-6)
+    for a, b, tol in ((gma, gmb, 1e-5), (gva, gvb, 1e-5), (gxa, gxb, 1e-4)):
+        assert _maxrel(a, b) < (1e-9 if f64 else 10 * tol)  # FP32: some cells differ after 80 cycles
+    assert np.abs(sa[0] - sb[0]).max() < (1e-12 if f64 else 1e-5)
