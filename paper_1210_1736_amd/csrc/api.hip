@@ -295,6 +295,7 @@ void free_particles(sbx_ctx* c) {
   c->acc_n = 0;
   c->n = 0;
   c->cur = 0;
+  c->ordered = false;
   c->com_fresh = false;
 }
 
@@ -464,13 +465,30 @@ sbx_status force_t(sbx_ctx* c, int mode) {
 
 // Reorder the particles by the cell of their finest grid, at the centres of
 // the last solve (or the current centre of mass before the first one).
+// rec: n records of eight values for particles that lie in no order yet
+// (borrowed ones: into the spare set; owned ones: rec is the spare set's own
+// block and they come back into the live set), or null.
 template <typename T>
-sbx_status sort_t(sbx_ctx* c) {
+sbx_status sort_t(sbx_ctx* c, T* rec) {
   const std::vector<InstInfo> info{info_of(c)};
   c->rec.mark(PH_START, c->stream);
   if (!c->solved) SBX_TRY(launch_centres<T>(dinst<T>(c), c->d_cur, info, false, c->stream, false));
-  SBX_TRY(launch_sort<T>(dinst<T>(c), c->d_cur, info, c->count, c->bins + 1, c->scan_tmp, c->stream));
-  c->cur ^= 1;
+  if (rec && sort_records_ok<T>(c->n)) {
+    const PSet& to = c->set[c->bound ? 1 : c->cur];
+    SBX_TRY(launch_sort_records<T>(dinst<T>(c), c->d_cur, info[0], pset_dev<T>(to, c->n), rec, c->count,
+                                   c->bins + 1, c->scan_tmp, c->stream));
+    c->cur ^= 1;
+    if (c->bound) {
+      SBX_TRY(launch_flip(c->d_cur, 1, c->stream));
+    } else {  // every reorder flips the live set: the two sets change places
+      std::swap(c->set[0], c->set[1]);
+      SBX_TRY(upload_inst(c));
+    }
+  } else {
+    SBX_TRY(launch_sort<T>(dinst<T>(c), c->d_cur, info, c->count, c->bins + 1, c->scan_tmp, c->stream));
+    c->cur ^= 1;
+  }
+  if (!c->bound) c->ordered = true;
   c->rec.mark(PH_SORT, c->stream);
   return SBX_OK;
 }
@@ -481,8 +499,9 @@ sbx_status field_solve(sbx_ctx* c) {
 sbx_status force(sbx_ctx* c, int mode) {
   return c->cfg.prec == SBX_FP64 ? force_t<double>(c, mode) : force_t<float>(c, mode);
 }
-sbx_status sort_particles(sbx_ctx* c) {
-  return c->cfg.prec == SBX_FP64 ? sort_t<double>(c) : sort_t<float>(c);
+sbx_status sort_particles(sbx_ctx* c, void* rec = nullptr) {
+  if (!c->bound) rec = c->ordered ? nullptr : c->set[c->cur ^ 1].block;
+  return c->cfg.prec == SBX_FP64 ? sort_t<double>(c, (double*)rec) : sort_t<float>(c, (float*)rec);
 }
 
 void free_recorder(Recorder& r) {
@@ -657,7 +676,7 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     lv_off = take(sizeof(double) * 3 * n);
     gm_off = take(sizeof(double) * n);
     dl_off = take(sizeof(double) * 4);
-    st_off = take(sizeof(double) * 3 * n);
+    st_off = take(sizeof(double) * 8 * n);
   };
   carve();
   if (c->adj_work_bytes < need) {
@@ -699,7 +718,7 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
     sort = rc == SBX_OK;  // without room for the copy the particles run as they are
   }
-  if (sort) SBX_TRY(sort_particles(c));
+  if (sort) SBX_TRY(sort_particles(c, stage));
   PSet& live = c->set[c->cur];
   // A record's fields are solved straight into it: each record has the
   // forward solves with their outputs there, and an instance whose fields
@@ -775,20 +794,24 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   }
   if (kept < nck) SBX_TRY(copy_set<T>(c, live, cks.back(), true, true));  // back to the final state
   if (c->bound && c->cur == 1)
-    SBX_TRY(launch_state_home<T>(pset_dev<T>(live, n), pset_dev<T>(c->set[0], n), c->stream));
+    SBX_TRY(launch_state_home<T>(pset_dev<T>(live, n), (T*)stage, pset_dev<T>(c->set[0], n), c->stream));
   c->com_fresh = false;
   c->grids_fields = false;
   c->step_count += nsteps;
   // outputs in the caller's order
   const int32_t* id = live.id;
   if (loss) SBX_HIP(hipMemcpyAsync(loss, dloss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  struct Out { double* host; double* dev; int w; } outs[3] = {{grad_m, gm, 1}, {grad_x, lx, 3}, {grad_v, lv, 3}};
-  for (auto& o : outs) {
-    if (!o.host) continue;
-    SBX_TRY(launch_unpermute<double>(o.dev, id, dev_out ? o.host : stage, n, o.w, c->stream));
-    if (!dev_out)
+  if (dev_out) {
+    if (grad_m || grad_x || grad_v)
+      SBX_TRY(launch_grads_out(id, n, gm, lx, lv, stage, grad_m, grad_x, grad_v, c->stream));
+  } else {
+    struct Out { double* host; double* dev; int w; } outs[3] = {{grad_m, gm, 1}, {grad_x, lx, 3}, {grad_v, lv, 3}};
+    for (auto& o : outs) {
+      if (!o.host) continue;
+      SBX_TRY(launch_unpermute<double>(o.dev, id, stage, n, o.w, c->stream));
       SBX_HIP(hipMemcpyAsync(o.host, stage, sizeof(double) * o.w * n, hipMemcpyDeviceToHost, c->stream));
-    SBX_HIP(hipStreamSynchronize(c->stream));
+      SBX_HIP(hipStreamSynchronize(c->stream));
+    }
   }
   SBX_HIP(hipStreamSynchronize(c->stream));
   return SBX_OK;

@@ -56,6 +56,7 @@ struct sbx_ctx {
   int64_t n = 0;
   sbx::PSet set[2];
   int cur = 0;
+  bool ordered = false;  // the live set has been put in cell order once
   bool bound = false;  // set[0] is the caller's storage (sbx_bind_device_particles)
   int* d_cur = nullptr;
   // grids

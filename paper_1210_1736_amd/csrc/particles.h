@@ -206,6 +206,17 @@ template <typename T>
 sbx_status launch_sort(const InstDev<T>* inst, int* cur, const std::vector<InstInfo>& info,
                        uint32_t* counts, size_t total_counts, uint32_t* tmp, hipStream_t s);
 
+// The same for one instance whose particles lie in no order at all (as the
+// caller gave them): through records of eight values at rec (n of them; see
+// the kernels) from the live set into dst, which may be that set.  cur is
+// left alone.  Needs sort_records_ok.
+template <typename T>
+sbx_status launch_sort_records(const InstDev<T>* inst, int* cur, const InstInfo& info, const PartDev<T>& dst,
+                               T* rec, uint32_t* counts, size_t total_counts, uint32_t* tmp, hipStream_t s);
+// A record's last value holds component, galaxy and flag beside the index.
+template <typename T>
+constexpr bool sort_records_ok(int64_t n) { return sizeof(T) == 8 || n <= ((int64_t)1 << 25); }
+
 // single-instance helpers
 template <typename T>
 sbx_status launch_indices(const InstDev<T>* inst, const int* cur, int64_t n, int galaxy, int level,
@@ -235,6 +246,9 @@ sbx_status launch_adj_step(const InstDev<T>* inst, int64_t n, const AdjCycle<T>&
 template <typename T>
 sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, const AdjCycle<T>& at,
                              const GridsDev<T>& P, double* gm, hipStream_t s);
+
+// Flip the live set of n instances.
+sbx_status launch_flip(int* cur, int n, hipStream_t s);
 
 sbx_status launch_iota(int32_t* id, int64_t n, hipStream_t s);
 
@@ -275,8 +289,16 @@ sbx_status launch_split3(const double* src, T* x0, T* x1, T* x2, int64_t n, hipS
 template <typename T>
 sbx_status launch_state_out(const PartDev<T>& p, T* rec, double* x, double* v, uint8_t* lost,
                             hipStream_t s);
-// Positions, velocities and lost flags of p back to its order's home set.
+// Positions, velocities and lost flags of p back to the rows id[i] of the set
+// it was sorted from (flags already raised there keep their value).  rec: n
+// records of eight values.
 template <typename T>
-sbx_status launch_state_home(const PartDev<T>& p, const PartDev<T>& home, hipStream_t s);
+sbx_status launch_state_home(const PartDev<T>& p, T* rec, const PartDev<T>& home, hipStream_t s);
+
+// Gradients in the caller's order: gm (n), lx and lv (n * 3) to the outputs
+// that are not null.  rec: n records of eight float64.
+sbx_status launch_grads_out(const int32_t* id, int64_t n, const double* gm, const double* lx,
+                            const double* lv, double* rec, double* out_m, double* out_x, double* out_v,
+                            hipStream_t s);
 
 }  // namespace sbx

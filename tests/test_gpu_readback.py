@@ -68,3 +68,37 @@ def test_forces_in_callers_order(sbx, prec, n):
     assert np.abs(a1 - a0).max() <= tol * scale and np.abs(p1 - p0).max() <= tol * np.abs(p0).max()
     assert not a1[lost].any() and not p1[lost].any() and (p1[~lost] < 0).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,n", [(0, 2 ** 25), (0, 2 ** 25 + 1), (1, 2 ** 20 + 1)])
+def test_first_reorder_keeps_every_particle(sbx, prec, n):
+    """The first reorder of particles in no order (through records up to 2^25
+    particles in FP32, by gathering above) and the ones after it: every value,
+    component, galaxy and flag still with its particle."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(1736 + n)
+    x = (torch.rand((n, 3), generator=g, device="cuda") * 2.1 - 1.05).double()
+    v = torch.rand((n, 3), generator=g, device="cuda").double()
+    m = torch.rand(n, generator=g, device="cuda").double() / n
+    comp = torch.randint(0, 8, (n,), generator=g, device="cuda", dtype=torch.int8)
+    gal = torch.zeros(n, device="cuda", dtype=torch.int8)
+    ctx = sbx.Context(prec=prec)
+    ctx.sbx_build_grids([sbx.make_hierarchy([(32, 1.0, 1.0)])])
+    torch.cuda.synchronize()
+    ctx.sbx_load_particles_device(n, x.data_ptr(), v.data_ptr(), m.data_ptr(), comp.data_ptr(), gal.data_ptr())
+    ctx.sbx_set_sort_interval(1)
+    xo, vo, lo = torch.empty_like(x), torch.empty_like(v), torch.empty(n, device="cuda", dtype=torch.uint8)
+    cell = torch.floor(x * 14.0 + 16.5)
+    lost = ((cell < 2) | (cell > 29)).any(1)
+    for _ in range(2):
+        ctx.sbx_step(0.0, 1, 1)
+        ctx.sbx_get_particles_device(xo.data_ptr(), vo.data_ptr(), lo.data_ptr())
+        assert bool((xo == x).all()) and bool((vo == v).all()) and bool((lo.bool() == lost).all())
+    d = ctx.sbx_diag_log()[-1]
+    live = ~lost
+    for c in range(8):
+        sel = live & (comp == c)
+        assert d["n_live"][c] == int(sel.sum())
+        ek = float((0.5 * m * (v * v).sum(1))[sel].sum())
+        assert d["ekin"][c] == pytest.approx(ek, rel=1e-6)  # v_sync of a step of no length is v
+    ctx.close()
