@@ -414,6 +414,7 @@ sbx_status build_grids_t(sbx_ctx* c) {
   if (dm) {
     c->dm_elems = cells * c->ngal;
     SBX_TRY(dev_alloc((void**)&c->dm_hist, sizeof(unsigned long long) * c->dm_elems));
+    SBX_HIP(hipMemsetAsync(c->dm_hist, 0, sizeof(unsigned long long) * c->dm_elems, c->stream));
     SBX_TRY(dev_alloc((void**)&c->dm_aux, sizeof(unsigned long long) * kDmAux));
     SBX_TRY(dev_alloc((void**)&c->dm_partial, sizeof(double) * (size_t)kRedBlocks * kPreVals));
   }

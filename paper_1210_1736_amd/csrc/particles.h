@@ -104,16 +104,15 @@ struct InstDev {
   uint32_t* count;          // bins + 1: this instance's slice of the shared counts
   uint32_t part_base;       // sort position of the instance's first particle
   // density-maximum centring (null / 0 when no galaxy uses it)
-  unsigned long long* dm_hist;  // ngal * N^3 integer cell masses of the inner grids
+  unsigned long long* dm_hist;  // ngal * N^3 integer cell masses of the inner grids (zero between steps)
   size_t dm_elems;
-  unsigned long long* dm_aux;   // [g] densest cell of galaxy g (all ones: none), then
-                                // kMaxGal * kArgParts (value, index) partials
+  unsigned long long* dm_aux;   // kMaxGal * kArgParts (value, index) partials of the search
   double* dm_partial;           // as pre_partial: block sums around the densest cell
   const unsigned long long* dm_mmax;  // bits of the largest particle mass (set at load)
   double dt;
   int64_t n;
 };
-constexpr int kDmAux = kMaxGal + 2 * kMaxGal * kArgParts;
+constexpr int kDmAux = 2 * kMaxGal * kArgParts;
 
 // Counting-sort bins.  A particle's bin is the cell of its finest grid
 // relative to its own galaxy; bins are ordered by galaxy, level, z, y, x,
