@@ -898,6 +898,15 @@ __global__ void __launch_bounds__(NT)
 // other's transforms (in FP64, whose whole plane does not fit, one runs).
 // Blocks 8 apart (one XCD) take the two halves of a plane, so the second
 // finds the rows in that XCD's L2.
+//
+// At N = 64 it takes the place of the whole-plane block of 256 threads as
+// two blocks of 128 (32 row pairs, then 32 columns, four lanes each: one
+// round without an idle group).  Either way 256 lanes a plane is what fits a
+// CU's LDS twice in FP64, so a set of 9 solves (576 planes) is 1.1 rounds of
+// the chip; with blocks half as long the second, nearly empty round costs half.
+// The pass of 9 FP64 solves 43.2 -> 28.0 us; 6 whole FP64 solves 55.5 -> 47.9 us
+// (20: 210 -> 185 us, 1: the same); 5 and 20 in FP32, where 4 whole planes fit a
+// CU, the same within the runs.
 template <typename T, int N>
 struct PH {
   static constexpr int V = 16, TL = N / V;
@@ -909,6 +918,7 @@ struct PH {
   static constexpr int XL = XLX > XLY ? XLX : XLY;
   static constexpr int XP = PL<T, N>::XP;
   static constexpr int LDS = XL + XP;
+  static constexpr bool fwd64 = N == 64;  // the forward pass, one round of 128 threads
   // FP32: two blocks per CU; FP64 (whose whole plane does not fit): one
   static constexpr bool fits = N == 128 && LDS * (int)sizeof(C2<T>) * (sizeof(T) == 4 ? 2 : 1) <= 160 * 1024;
 };
@@ -1636,13 +1646,20 @@ static void launch_plane_n(bool inv, const SolveDesc<T>* solves, int nsolves, in
         return;
       }
     }
+    if constexpr (PH<T, N>::fwd64) {
+      if (!inv && nt == 256) {  // 256 threads per plane, as two blocks
+        hipLaunchKernelGGL((k_plane_fwd_h<T, N, 128>), dim3(2 * nsolves * N), dim3(128), 0, st, solves, reset, tw,
+                           twist);
+        return;
+      }
+    }
     if constexpr (PL<T, N>::fits) {  // whole planes (FP64 at N = 128 has none)
       auto go = [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
         if (inv)
           hipLaunchKernelGGL((k_plane_inv<T, N, NT>), dim3(nsolves * N), dim3(NT), 0, st, solves, reset, tw,
                              twist);
-        else
+        else if constexpr (!(PH<T, N>::fwd64 && NT == 256))
           hipLaunchKernelGGL((k_plane_fwd<T, N, NT>), dim3(nsolves * N), dim3(NT), 0, st, solves, reset, tw,
                              twist);
       };

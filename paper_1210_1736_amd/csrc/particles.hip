@@ -738,7 +738,7 @@ __global__ void __launch_bounds__(256)
     }
   }
   // Particles lie in cell order, so most blocks have none in any window
-  // and skip the block sums of their zeros (17.7 -> 15.3 us at 400k particles).
+  // and skip the block sums of their zeros (17.7 -> 15.3 us at 10^6 particles).
   if (!__syncthreads_or(hit)) {
     if (threadIdx.x < kPreVals) I.dm_partial[(size_t)threadIdx.x * kRedBlocks + lb] = 0.0;
     return;
