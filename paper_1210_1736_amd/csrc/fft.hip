@@ -429,6 +429,10 @@ __device__ __forceinline__ void tile_fwd_y(const SolveDesc<T>& d, int tile, C2<T
 // the footprint in the caches, and the loads are plain ones since the lines
 // come back as stores (five 128^3 FP32 solves 215 -> 212 us, sixteen 64^3
 // 81 -> 76 us, six 64^3 FP64 57 -> 55-56 us).
+// Hhat is loaded with the line, before the forward transform: a compute unit
+// holds two tiles at a time, too few to cover a second round trip to memory
+// in mid-tile (five 128^3 FP32 solves 211.5 -> 195.5 us, six 64^3 FP64
+// 47.9 -> 44.9 us, one 256^3 FP64 858 -> 840 us).
 template <typename T, int L, int V, int NT, bool PLANE>
 __device__ __forceinline__ void tile_zpass(const SolveDesc<T>& d, int tile, C2<T>* s,
                                            const C2<T>* __restrict__ tw) {
@@ -438,28 +442,48 @@ __device__ __forceinline__ void tile_zpass(const SolveDesc<T>& d, int tile, C2<T
   constexpr int RL = F::template R<NP - 1>, NBL = L / RL;
   const int tid = threadIdx.x, t = tid % TL, w = tid / TL;
   const int kx = tile / (L / W), ky0 = (tile % (L / W)) * W;
+  static_assert(W * TL <= NT, "a line per TL threads");
+  const int kyl = ky0 + w;
+  // the frequency of line w along y
+  const int ky = PLANE ? (kyl < N ? 2 * kyl : 2 * (kyl - N) + 1) : kyl;
+  C2<T> v[F::VPT];
   if constexpr (PLANE) {
     const gp<const C2<T>> __restrict__ g = glb(d.C + (size_t)kx * N * L + ky0);
-    for (int i = tid; i < W * N; i += NT) {
-      const int z = i / W, ww = i - z * W;
-      const gp<const C2<T>> e = g + (size_t)z * L + ww;
-      s[ww * P + pad(z)] = gld(e);
+#pragma unroll
+    for (int r = 0; r < (W * N + NT - 1) / NT; ++r) {
+      const int i = tid + r * NT, z = i / W, ww = i - z * W;
+      if (i < W * N) v[r] = gld(g + ((size_t)z * L + ww));
+    }
+  } else if (w < W) {
+    const gp<const C2<T>> __restrict__ g = glb(d.C + ((size_t)kx * L + ky) * N);
+#pragma unroll
+    for (int r = 0; r < F::VPT; ++r) v[r] = r < F::VPT / 2 ? C2<T>{__builtin_nontemporal_load(&g[t + r * TL].re), __builtin_nontemporal_load(&g[t + r * TL].im)} : C2<T>{(T)0, (T)0};
+  }
+  // Hhat at frequencies (kx, ky, e), e = j + r L/R of the last pass
+  T hh[F::VPT];
+  if (w < W) {
+    const gp<const T> __restrict__ H = glb(d.H + ((size_t)kx * (N + 1) + (ky <= N ? ky : L - ky)) * (N + 1));
+#pragma unroll
+    for (int b = 0; b < F::VPT / RL; ++b)
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        const int e = t + b * TL + r * NBL;
+        hh[b * RL + r] = H[e <= N ? e : L - e];
+      }
+  }
+  if constexpr (PLANE) {
+#pragma unroll
+    for (int r = 0; r < (W * N + NT - 1) / NT; ++r) {
+      const int i = tid + r * NT, z = i / W, ww = i - z * W;
+      if (i < W * N) s[ww * P + pad(z)] = v[r];
     }
     __syncthreads();
   }
   if (w < W) {
-    const int kyl = ky0 + w;
-    // the frequency of line w along y
-    const int ky = PLANE ? (kyl < N ? 2 * kyl : 2 * (kyl - N) + 1) : kyl;
     C2<T>* sl = s + w * P;
-    C2<T> v[F::VPT];
     if constexpr (PLANE) {
 #pragma unroll
       for (int r = 0; r < F::VPT; ++r) v[r] = r < F::VPT / 2 ? sl[pad(t + r * TL)] : C2<T>{(T)0, (T)0};
-    } else {
-      const gp<const C2<T>> __restrict__ g = glb(d.C + ((size_t)kx * L + ky) * N);
-#pragma unroll
-      for (int r = 0; r < F::VPT; ++r) v[r] = r < F::VPT / 2 ? C2<T>{__builtin_nontemporal_load(&g[t + r * TL].re), __builtin_nontemporal_load(&g[t + r * TL].im)} : C2<T>{(T)0, (T)0};
     }
     if constexpr (NP > 1) {
       fwd_bfly<T, L, V, 0>(v, t, tw);
@@ -476,15 +500,8 @@ __device__ __forceinline__ void tile_zpass(const SolveDesc<T>& d, int tile, C2<T
       }
     }
     fwd_bfly<T, L, V, NP - 1>(v, t, tw);
-    // Hhat at frequencies (kx, ky, e), e = j + r L/R of the last pass
-    const gp<const T> __restrict__ H = glb(d.H + ((size_t)kx * (N + 1) + (ky <= N ? ky : L - ky)) * (N + 1));
 #pragma unroll
-    for (int b = 0; b < F::VPT / RL; ++b)
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int e = t + b * TL + r * NBL;
-        v[b * RL + r] = cscale(v[b * RL + r], H[e <= N ? e : L - e]);
-      }
+    for (int r = 0; r < F::VPT; ++r) v[r] = cscale(v[r], hh[r]);
     inv_down<T, L, V, NP - 1>(sl, t, v, tw);
     wave_sync();
 #pragma unroll
