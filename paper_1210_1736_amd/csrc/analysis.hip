@@ -38,8 +38,11 @@ __global__ void __launch_bounds__(256)
     const bool sel = in && p.comp[i] == comp && p.gal[i] == gal && !p.lost[i];
     const uint64_t bits = __ballot(sel);
     const int32_t id0 = __builtin_amdgcn_readfirstlane(id);
-    if (__ballot(in && id != id0 + lane) == 0ull && (id0 & 63) == 0) {
-      // the caller's own order: this wavefront owns its words
+    const int here = p.n - w * 64 < 64 ? (int)(p.n - w * 64) : 64;
+    if (__ballot(in && id != id0 + lane) == 0ull && (id0 & 63) == 0 && (here == 64 || id0 + here == p.n)) {
+      // the caller's own order: this wavefront holds every number of its
+      // words.  The last one, if it is not full, does so only where its
+      // numbers are the highest: the rest of its words lies elsewhere else.
       if (in && (lane & 31) == 0) mask[id >> 5] = (uint32_t)(bits >> lane);
     } else if (sel) {
       __hip_atomic_fetch_or(mask + (id >> 5), 1u << (id & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
