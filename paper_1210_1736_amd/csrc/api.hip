@@ -478,18 +478,16 @@ sbx_status sort_t(sbx_ctx* c, T* rec) {
     const PSet& to = c->set[c->bound ? 1 : c->cur];
     SBX_TRY(launch_sort_records<T>(dinst<T>(c), c->d_cur, info[0], pset_dev<T>(to, c->n), rec, c->count,
                                    c->bins + 1, c->scan_tmp, c->stream));
-    c->cur ^= 1;
     if (c->bound) {
       SBX_TRY(launch_flip(c->d_cur, 1, c->stream));
     } else {  // every reorder flips the live set: the two sets change places
+      SBX_TRY(launch_swap_sets<T>((InstDev<T>*)c->d_inst, c->d_cur, c->stream));
       std::swap(c->set[0], c->set[1]);
-      SBX_TRY(upload_inst(c));
     }
   } else {
     SBX_TRY(launch_sort<T>(dinst<T>(c), c->d_cur, info, c->count, c->bins + 1, c->scan_tmp, c->stream));
-    c->cur ^= 1;
   }
-  if (!c->bound) c->ordered = true;
+  c->cur ^= 1;
   c->rec.mark(PH_SORT, c->stream);
   return SBX_OK;
 }
@@ -500,9 +498,21 @@ sbx_status field_solve(sbx_ctx* c) {
 sbx_status force(sbx_ctx* c, int mode) {
   return c->cfg.prec == SBX_FP64 ? force_t<double>(c, mode) : force_t<float>(c, mode);
 }
+// Owned particles take the records once, while they lie in the caller's order.
+// A step under stream capture keeps the gather, whose launches name no set:
+// its replays find the live set through the device's index.
 sbx_status sort_particles(sbx_ctx* c, void* rec = nullptr) {
-  if (!c->bound) rec = c->ordered ? nullptr : c->set[c->cur ^ 1].block;
-  return c->cfg.prec == SBX_FP64 ? sort_t<double>(c, (double*)rec) : sort_t<float>(c, (float*)rec);
+  bool first = false;
+  if (!c->bound) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(c->stream, &cap) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    first = !c->ordered && known && cap == hipStreamCaptureStatusNone;
+    rec = first ? c->set[c->cur ^ 1].block : nullptr;
+  }
+  SBX_TRY(c->cfg.prec == SBX_FP64 ? sort_t<double>(c, (double*)rec) : sort_t<float>(c, (float*)rec));
+  if (first) c->ordered = true;
+  return SBX_OK;
 }
 
 void free_recorder(Recorder& r) {

@@ -248,6 +248,9 @@ sbx_status launch_adj_gather(const InstDev<T>* inst, const int* cur, int64_t n, 
 
 // Flip the live set of n instances.
 sbx_status launch_flip(int* cur, int n, hipStream_t s);
+// The two sets of one instance change places and the live one is flipped.
+template <typename T>
+sbx_status launch_swap_sets(InstDev<T>* inst, int* cur, hipStream_t s);
 
 sbx_status launch_iota(int32_t* id, int64_t n, hipStream_t s);
 

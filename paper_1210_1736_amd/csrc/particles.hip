@@ -1361,6 +1361,14 @@ __global__ void k_flip(int* cur, int n) {
   if ((int)threadIdx.x < n) cur[threadIdx.x] ^= 1;
 }
 
+template <typename T>
+__global__ void k_swap_sets(InstDev<T>* inst, int* cur) {
+  const PartDev<T> a = inst->p[0];
+  inst->p[0] = inst->p[1];
+  inst->p[1] = a;
+  *cur ^= 1;
+}
+
 
 // ---------------------------------------------------------------- adjoint --
 // Reverse mode of one integration cycle (see the oracle's derivation):
@@ -2084,6 +2092,15 @@ sbx_status launch_flip(int* cur, int n, hipStream_t s) {
   SBX_HIP(hipGetLastError());
   return SBX_OK;
 }
+
+template <typename T>
+sbx_status launch_swap_sets(InstDev<T>* inst, int* cur, hipStream_t s) {
+  hipLaunchKernelGGL((k_swap_sets<T>), dim3(1), dim3(1), 0, s, inst, cur);
+  SBX_HIP(hipGetLastError());
+  return SBX_OK;
+}
+template sbx_status launch_swap_sets<float>(InstDev<float>*, int*, hipStream_t);
+template sbx_status launch_swap_sets<double>(InstDev<double>*, int*, hipStream_t);
 
 sbx_status launch_iota(int32_t* id, int64_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_iota, dim3(2048), dim3(256), 0, s, id, n);
