@@ -2020,8 +2020,16 @@ static sbx_status tune_group(const SolveDesc<T>* d_solves, const SolveDesc<T>* h
   }
   // Within 5% (the spread of these timings from one process to the next)
   // the form that moves fewer bytes wins: the plane form, whose margin
-  // inside a step has been larger than in this isolated comparison.
-  out = (plane && (!five || t3 < 1.05f * t5)) ? plane_t : five_t;
+  // inside a step has been larger than in this isolated comparison.  Below
+  // 64^3 the sets lie in the caches and bytes do not decide: there the plane
+  // form has to be 10% ahead.  One to five solves of 32^3 in FP32 time within
+  // 13% of each other here (24.4 us in line passes, 25.5 in the plane form for
+  // four; the same plan called again and again: 21.5 and 22.4), 16 take 36
+  // against 31 us.  With such ties on the other side, plans of few solves fell
+  // to one form or the other from process to process, and a batch was no
+  // longer bit for bit its grids solved alone.
+  const float lead = N >= 64 ? 1.05f : 0.9f;
+  out = (plane && (!five || t3 < lead * t5)) ? plane_t : five_t;
   out.ms5 = five ? t5 : 0.f;
   out.ms3 = plane ? t3 : 0.f;
   (void)hipEventDestroy(e0);
