@@ -14,8 +14,8 @@
 // Where a z plane's half spectrum fits in LDS (32 <= N <= 64; at N = 128
 // half of it, in FP32 and FP64) the same solve can run in three passes: plane forward (x and y of
 // one plane in one block) -> P[z][kx][ky'] (in C; ky' = m for ky = 2m,
-// N + m for 2m + 1), the z pass on that layout in place, plane inverse
-// (inverse y and x of one plane) -> phi.  At N = 128 the plane passes can run as
+// N + m for 2m + 1), the z pass on that layout (in place, or to D for small
+// grids), plane inverse (inverse y and x of one plane) -> phi.  At N = 128 the plane passes can run as
 // two blocks per plane, each in half the LDS (two such blocks per CU in
 // FP32, one in FP64, whose whole plane does not fit): the forward one for
 // the even and one for the odd kx columns, the inverse one for the even

@@ -419,16 +419,28 @@ __device__ __forceinline__ void tile_fwd_y(const SolveDesc<T>& d, int tile, C2<T
   }
 }
 
+// Whether the z pass of the plane form works in place (on C) or writes D:
+// where one solve's spectrum is 8 MB and more (64^3 in FP64, 128^3).  Through
+// D against in place: 192-218 against 182 us (five 128^3 FP32 solves), 162
+// against 147 (two 128^3 FP64), 46.6 against 44.7 (six 64^3 FP64, three plans
+// in turn).  Smaller ones fit the XCDs' L2, and lines that come from one
+// XCD's and go to another's cost more in place than the second buffer: one
+// plan of 64^3 FP32 solves again and again takes 39.7, 41.0, 42.8 and 55.8 us
+// through D for 4, 5, 6 and 9 solves, 42.8, 48.2, 52.4 and 62.0 in place (with
+// three plans in turn alike up to 9, and 72 against 66 us for 16); 24 of 32^3
+// in FP64 58.9 against 62.6.
+template <typename T, int N>
+constexpr bool z_in_place = N * sizeof(T) >= 512;
+
 // zpass: tile = W consecutive ky at one kx, one line per TL threads; forward
 // z (input z < N) from global, times Hhat in registers, inverse z, keep
 // z < N; stored transposed as D[kx][z][ky] through LDS.
 // PLANE: the spectra of the plane-fused passes, P[kx][z][ky'] in and out
 // (ky' = m for ky = 2m, N + m for ky = 2m + 1): a tile's W lines are W
 // consecutive ky' at one kx, gathered along z through LDS in runs of W
-// from one kx slab.  A tile writes where it read, so it works in place: half
-// the footprint in the caches, and the loads are plain ones since the lines
-// come back as stores (five 128^3 FP32 solves 215 -> 212 us, sixteen 64^3
-// 81 -> 76 us, six 64^3 FP64 57 -> 55-56 us).
+// from one kx slab.  A tile writes where it read, so it can work in place
+// (z_in_place): half the footprint in the caches, and plain loads since the
+// lines come back as stores.
 // Hhat is loaded with the line, before the forward transform: a compute unit
 // holds two tiles at a time, too few to cover a second round trip to memory
 // in mid-tile (five 128^3 FP32 solves 211.5 -> 195.5 us, six 64^3 FP64
@@ -452,7 +464,11 @@ __device__ __forceinline__ void tile_zpass(const SolveDesc<T>& d, int tile, C2<T
 #pragma unroll
     for (int r = 0; r < (W * N + NT - 1) / NT; ++r) {
       const int i = tid + r * NT, z = i / W, ww = i - z * W;
-      if (i < W * N) v[r] = gld(g + ((size_t)z * L + ww));
+      if (i < W * N) {
+        const gp<const C2<T>> e = g + ((size_t)z * L + ww);
+        if constexpr (z_in_place<T, N>) v[r] = gld(e);
+        else v[r] = C2<T>{__builtin_nontemporal_load(&e->re), __builtin_nontemporal_load(&e->im)};
+      }
     }
   } else if (w < W) {
     const gp<const C2<T>> __restrict__ g = glb(d.C + ((size_t)kx * L + ky) * N);
@@ -509,7 +525,7 @@ __device__ __forceinline__ void tile_zpass(const SolveDesc<T>& d, int tile, C2<T
   }
   __syncthreads();
   if constexpr (PLANE) {
-    const gp<C2<T>> dst = glb(d.C + (size_t)kx * N * L + ky0);
+    const gp<C2<T>> dst = glb((z_in_place<T, N> ? d.C : d.D) + (size_t)kx * N * L + ky0);
     for (int i = tid; i < W * N; i += NT) {
       const int z = i / W, ww = i - z * W;
       gst(dst + (size_t)z * L + ww, s[ww * P + pad(z)]);
@@ -634,8 +650,9 @@ __device__ __forceinline__ void tile_inv_x(const SolveDesc<T>& d, int tile, C2<T
 // The plane's spectrum in LDS is column-major, slot(kx, y) = col(kx) +
 // pad(y) for kx < N; column 0 holds X(0) + i X(N), both real for a real
 // row.  Between the passes the spectra are P[kx][z][ky'] (kx <= N, in the
-// C buffer), ky' = m for ky = 2m and N + m for ky = 2m + 1: a plane
-// writes one 2N run per kx, and a z tile reads within one kx slab.
+// C buffer, after the z pass in C or D: z_in_place), ky' = m for ky = 2m and
+// N + m for 2m + 1: a plane writes one 2N run per kx, and a z tile reads
+// within one kx slab.
 template <typename T>
 struct PadLine {  // one line of LDS in natural order, one pad per 16
   C2<T>* b;
@@ -1080,6 +1097,7 @@ __global__ void __launch_bounds__(NT)
   __shared__ C2<T> s[G::LDS];
   if (reset && blockIdx.x == 0 && threadIdx.x == 0) *reset = 0;
   const SolveDesc<T>& d = solves[blockIdx.x / N];
+  const C2<T>* const P = z_in_place<T, N> ? d.C : d.D;
   const int z = blockIdx.x % N;
   const int tid = threadIdx.x, t = tid % TL, grp = tid / TL;
   // y: column kx from its even and odd frequencies (column 0 from
@@ -1100,8 +1118,8 @@ __global__ void __launch_bounds__(NT)
 #pragma unroll
     for (int c = 0; c < GPW; ++c) {
       const int kc = k0 + wc0 + c;
-      const gp<const C2<T>> q = glb(d.C + ((size_t)kc * N + z) * L);
-      const gp<const C2<T>> qn = glb(d.C + ((size_t)N * N + z) * L);
+      const gp<const C2<T>> q = glb(P + ((size_t)kc * N + z) * L);
+      const gp<const C2<T>> qn = glb(P + ((size_t)N * N + z) * L);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1223,6 +1241,7 @@ __global__ void __launch_bounds__(NT)
   const int bq = blockIdx.x >> 3, hp = bq & 1;
   const int plane = (bq >> 1) * 8 + (blockIdx.x & 7);
   const SolveDesc<T>& d = solves[plane / N];
+  const C2<T>* const P = z_in_place<T, N> ? d.C : d.D;
   const int z = plane % N;
   const int tid = threadIdx.x, lane = tid & 63;
   // y: column kx at slots col(kx) + pad(p), p = 0..N/2-1.  The wavefront
@@ -1242,8 +1261,8 @@ __global__ void __launch_bounds__(NT)
 #pragma unroll
       for (int c = 0; c < GPWH; ++c) {
         const int kc = k0 + wc0 + c;
-        const gp<const C2<T>> q = glb(d.C + ((size_t)kc * N + z) * L);
-        const gp<const C2<T>> qn = glb(d.C + ((size_t)N * N + z) * L);
+        const gp<const C2<T>> q = glb(P + ((size_t)kc * N + z) * L);
+        const gp<const C2<T>> qn = glb(P + ((size_t)N * N + z) * L);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           C2<T> e0 = gld(q + (h * N + lane)), e1 = gld(q + (h * N + H + lane));
@@ -2021,14 +2040,13 @@ static sbx_status tune_group(const SolveDesc<T>* d_solves, const SolveDesc<T>* h
   // Within 5% (the spread of these timings from one process to the next)
   // the form that moves fewer bytes wins: the plane form, whose margin
   // inside a step has been larger than in this isolated comparison.  Below
-  // 64^3 the sets lie in the caches and bytes do not decide: there the plane
-  // form has to be 10% ahead.  One to five solves of 32^3 in FP32 time within
-  // 13% of each other here (24.4 us in line passes, 25.5 in the plane form for
-  // four; the same plan called again and again: 21.5 and 22.4), 16 take 36
-  // against 31 us.  With such ties on the other side, plans of few solves fell
-  // to one form or the other from process to process, and a batch was no
-  // longer bit for bit its grids solved alone.
-  const float lead = N >= 64 ? 1.05f : 0.9f;
+  // 64^3 the sets lie in the caches and bytes do not decide, so there the
+  // faster one wins.  One, four and eight solves of 32^3 in FP32 come out 12,
+  // 8 and 3% slower in the plane form, 16 are 6% faster: with ties on the
+  // plane form's side, plans of a few solves can fall to different forms from
+  // process to process, and a batch is then no longer bit for bit its grids
+  // solved alone.
+  const float lead = N >= 64 ? 1.05f : 1.f;
   out = (plane && (!five || t3 < lead * t5)) ? plane_t : five_t;
   out.ms5 = five ? t5 : 0.f;
   out.ms3 = plane ? t3 : 0.f;
