@@ -166,10 +166,13 @@ sbx_status sbx_load_particles_device(sbx_ctx* ctx, int64_t n, const double* x, c
  * the context stream; getters copy from them.  The storage is borrowed until
  * sbx_destroy or the next sbx_load_particles*, sbx_bind_device_particles or
  * sbx_load: the caller keeps it alive and orders its own work on it with the
- * context stream.  Bound particles are never reordered (steps skip the cell
- * sort, a performance setting only; a differentiable segment runs on a sorted
- * copy of its own), and a context holding them cannot join a batch.  Validated on the device as sbx_load_particles_device
- * (SBX_EINVAL); x, v and lost must not overlap any other array (SBX_EINVAL).
+ * context stream.  Bound particles are never reordered: steps skip the cell
+ * sort, a performance setting only, and a differentiable segment runs on a
+ * sorted copy that the context keeps (43 or 71 bytes a particle in FP32 or
+ * FP64, the sort's arrays included; without room for it the segment runs in
+ * the caller's order).  A context holding them cannot join a batch.  Validated
+ * on the device as sbx_load_particles_device (SBX_EINVAL); x, v and lost must
+ * not overlap any other array (SBX_EINVAL).
  * Lost flags are taken as given. */
 sbx_status sbx_bind_device_particles(sbx_ctx* ctx, int64_t n, void* x, void* v, void* m,
                                      int8_t* comp, int8_t* gal, uint8_t* lost);
@@ -229,9 +232,13 @@ sbx_status sbx_diag_log(sbx_ctx* ctx, int32_t max, sbx_diag* out, int32_t* count
 
 /* Differentiable segment: nsteps integration cycles from the current state
  * (no reordering inside), then the reverse mode of the discrete cycles.  The
- * last cycles' positions and fields are kept from the forward (those of the
- * last ckpt_every cycles, and of more where 4 GiB hold them); the others are
- * recomputed from (x, v) checkpoints every ckpt_every steps.  Loss L = sum over the live particles of component
+ * last ckpt_every cycles' positions and fields are kept from the forward; the
+ * others are recomputed from (x, v) checkpoints every ckpt_every steps.  A
+ * work buffer for these stays with the context until its particles or grids
+ * are replaced.  While the call runs it may hold the records of earlier cycles
+ * as well, instead of recomputing them, in up to 4 GiB and at most an eighth
+ * of the device memory that is free then; they are given back before it
+ * returns.  Loss L = sum over the live particles of component
  * sel_comp of galaxy sel_gal of 1/2 m v_z^2, with v the staggered velocity
  * after the last kick.  Outputs (host, caller's particle order, any may be
  * NULL): loss (1), grad_m = dL/dm (n), grad_x = dL/dx (n*3) and
@@ -268,7 +275,9 @@ sbx_status sbx_adjoint_segment_device(sbx_ctx* ctx, double dt, int32_t nsteps, i
  *     annulus means, sigma_tot^2, and the vertical density profile: mass in
  *     n_z equal bins of z over [-z_max, z_max) over (annulus area x bin
  *     width).
- * Every sum is reduced in a fixed order except the profile bins.  Outputs on
+ * Every sum is reduced in a fixed order except the profile bins.  The work
+ * buffer (some 65 or 97 bytes a disc particle in FP32 or FP64) stays with the
+ * context until its particles are replaced.  Outputs on
  * the host: bin_r, bin_vc, bin_rms_z (n_bins each) and rho_z (n_z), any may
  * be NULL.  SBX_EINVAL for a bad query (1 <= n_bins <= 2048,
  * 1 <= n_z <= 1024, z_max > 0, 0 <= R_lo < R_hi), SBX_ESTATE without disc

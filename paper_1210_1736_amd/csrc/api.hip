@@ -630,16 +630,30 @@ sbx_status ensure_sort_arrays(sbx_ctx* c) {
   return upload_inst(c);
 }
 
-// Records the forward of a segment may keep beyond its last interval.
+// Records the forward of a segment may keep beyond its last interval, and the
+// part of the device's free memory it leaves alone.
 constexpr size_t kKeepBytes = (size_t)4 << 30;
+constexpr size_t kKeepShare = 8;  // one eighth of it at most
+
+// A device buffer of one call, given back when the call ends.
+struct CallBuffer {
+  hipStream_t s;
+  void* p = nullptr;
+  ~CallBuffer() {
+    if (!p) return;
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(p);
+  }
+};
 
 // Forward nsteps without sorting, then the reverse cycles interval by
-// interval.  The positions, lost flags and fields of the last intervals'
-// cycles are kept from the forward pass, as many intervals as kKeepBytes
-// hold besides the last one; those of the others are recomputed from
-// checkpoints of (x, v, lost) every ckpt_every steps (with the records of
-// all three intervals kept, a six-cycle segment on a 256^3 grid runs 12
-// solves instead of 16):
+// interval.  The positions, lost flags and fields of the last interval's
+// cycles are kept from the forward pass, and those of the intervals before it
+// as far as kKeepBytes and an eighth of the free device memory hold them, in
+// a buffer of the call's own (allocating and freeing 4 GiB takes 0.3 ms each;
+// the solves it saves a six-cycle segment on a 256^3 grid, 12 instead of 16,
+// take 1.5); those of the others are recomputed from checkpoints of (x, v, lost)
+// every ckpt_every steps:
 // each cycle's solve runs from the particles that take part in it (live
 // after its start-of-step loss test), and its lost flags and fields are kept
 // for the reverse cycle, which scatters the adjoint sources, solves them and
@@ -662,65 +676,6 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   const size_t pitch = row_pitch(n, sizeof(T)), set_x = 3 * pitch;
   const size_t gbytes = sizeof(T) * c->grid_elems;
   SolvePlan<T>& fwd = sizeof(T) == 8 ? (SolvePlan<T>&)c->plan64 : (SolvePlan<T>&)c->plan32;
-  // intervals whose records the forward keeps: the last one, and the ones
-  // before it as far as kKeepBytes go
-  const size_t rec_bytes = set_x + n + gbytes;
-  int kept = (int)std::min<size_t>(nck, 1 + kKeepBytes / (rec_bytes * ckpt));
-  // carve the work buffer: checkpoints (x, v, lost) of the intervals that are
-  // recomputed and the final state, records (x, lost, fields), their solve
-  // descriptors and instance records, adjoint state, loss, staging
-  size_t need, lx_off, lv_off, gm_off, dl_off, st_off, sd_off, in_off;
-  std::vector<size_t> ck_off, xb_off, fb_off;
-  auto carve = [&]() {
-    need = 0;
-    auto take = [&](size_t bytes) { const size_t at = need; need += (bytes + 255) & ~(size_t)255; return at; };
-    const int slots = std::min(kept * ckpt, nsteps);
-    ck_off.resize(kept < nck ? nck - kept + 1 : 0);
-    xb_off.resize(slots);
-    fb_off.resize(slots);
-    for (auto& o : ck_off) o = take(2 * set_x + n);
-    for (auto& o : xb_off) o = take(set_x + n);
-    for (auto& o : fb_off) o = take(gbytes);
-    sd_off = take(sizeof(SolveDesc<T>) * fwd.nsolves * slots);
-    in_off = take(sizeof(InstDev<T>) * slots);
-    lx_off = take(sizeof(double) * 3 * n);
-    lv_off = take(sizeof(double) * 3 * n);
-    gm_off = take(sizeof(double) * n);
-    dl_off = take(sizeof(double) * 4);
-    st_off = take(sizeof(double) * 8 * n);
-  };
-  carve();
-  if (c->adj_work_bytes < need) {
-    free_ptr(c->adj_work);
-    c->adj_work_bytes = 0;
-    sbx_status rc = dev_alloc(&c->adj_work, need);
-    if (rc == SBX_ENOMEM && kept > 1) {  // the last interval only
-      kept = 1;
-      carve();
-      rc = dev_alloc(&c->adj_work, need);
-    }
-    SBX_TRY(rc);
-    c->adj_work_bytes = need;
-  }
-  char* base = (char*)c->adj_work;
-  auto set_at = [&](size_t off, bool with_v, PSet& s) {
-    char* q = base + off;
-    for (int k = 0; k < 3; ++k) s.x[k] = q + pitch * k;
-    q += set_x;
-    if (with_v) {
-      for (int k = 0; k < 3; ++k) s.v[k] = q + pitch * k;
-      q += set_x;
-    }
-    s.lost = (uint8_t*)q;
-  };
-  std::vector<PSet> cks(ck_off.size()), xb(xb_off.size());
-  for (size_t i = 0; i < cks.size(); ++i) set_at(ck_off[i], true, cks[i]);
-  for (size_t i = 0; i < xb.size(); ++i) set_at(xb_off[i], false, xb[i]);
-  double* lx = (double*)(base + lx_off);
-  double* lv = (double*)(base + lv_off);
-  double* gm = (double*)(base + gm_off);
-  double* dloss = (double*)(base + dl_off);
-  double* stage = (double*)(base + st_off);
   // reorder by cell once for the segment (locality of the gathers and of
   // the adjoint scatter); nothing is reordered inside the segment
   bool sort = c->sort_every > 0;
@@ -729,17 +684,94 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
     sort = rc == SBX_OK;  // without room for the copy the particles run as they are
   }
-  if (sort) SBX_TRY(sort_particles(c, stage));
+  // carve the work buffer: checkpoints (x, v, lost) of the intervals but the
+  // last and the final state, one interval's records (x, lost, fields), their
+  // solve descriptors and instance records, adjoint state, loss, staging
+  size_t need = 0;
+  auto take = [&](size_t bytes) { const size_t at = need; need += (bytes + 255) & ~(size_t)255; return at; };
+  const int base_slots = std::min(ckpt, nsteps);
+  std::vector<size_t> ck_off(nck > 1 ? nck : 0), x_off(base_slots), f_off(base_slots);
+  for (auto& o : ck_off) o = take(2 * set_x + n);
+  for (auto& o : x_off) o = take(set_x + n);
+  for (auto& o : f_off) o = take(gbytes);
+  const size_t sd_off = take(sizeof(SolveDesc<T>) * fwd.nsolves * base_slots);
+  const size_t in_off = take(sizeof(InstDev<T>) * base_slots);
+  const size_t lx_off = take(sizeof(double) * 3 * n), lv_off = take(sizeof(double) * 3 * n);
+  const size_t gm_off = take(sizeof(double) * n), dl_off = take(sizeof(double) * 4);
+  const size_t st_off = take(sizeof(double) * 8 * n);
+  if (c->adj_work_bytes < need) {
+    free_ptr(c->adj_work);
+    c->adj_work_bytes = 0;
+    SBX_TRY(dev_alloc(&c->adj_work, need));
+    c->adj_work_bytes = need;
+  }
+  char* base = (char*)c->adj_work;
+  double* lx = (double*)(base + lx_off);
+  double* lv = (double*)(base + lv_off);
+  double* gm = (double*)(base + gm_off);
+  double* dloss = (double*)(base + dl_off);
+  double* stage = (double*)(base + st_off);
+  if (sort) SBX_TRY(sort_particles(c, stage));  // runs while the host allocates below
+  // intervals whose records the forward keeps: the last one, and the ones
+  // before it that the call's own buffer holds (records, and the descriptors
+  // and instance records of all)
+  const size_t slot_bytes = set_x + n + gbytes + sizeof(SolveDesc<T>) * fwd.nsolves + sizeof(InstDev<T>) + 1024;
+  int kept = 1;
+  CallBuffer more{c->stream};
+  if (nck > 1) {
+    size_t free_now = 0, total = 0;
+    if (hipMemGetInfo(&free_now, &total) != hipSuccess) {
+      (void)hipGetLastError();
+      free_now = 0;
+    }
+    const size_t room = std::min(kKeepBytes, free_now / kKeepShare);
+    kept = (int)std::min<size_t>(nck, 1 + room / (slot_bytes * ckpt));
+  }
+  int slots = (int)std::min<int64_t>((int64_t)kept * ckpt, nsteps);
+  size_t more_sd = 0, more_in = 0;
+  if (slots > base_slots) {
+    need = 0;
+    x_off.resize(slots);
+    f_off.resize(slots);
+    for (int i = base_slots; i < slots; ++i) {
+      x_off[i] = take(set_x + n);
+      f_off[i] = take(gbytes);
+    }
+    more_sd = take(sizeof(SolveDesc<T>) * fwd.nsolves * slots);
+    more_in = take(sizeof(InstDev<T>) * slots);
+    const sbx_status rc = dev_alloc(&more.p, need);
+    if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
+    if (rc != SBX_OK) {  // the last interval only
+      kept = 1;
+      slots = base_slots;
+    }
+  }
+  auto slot_at = [&](const std::vector<size_t>& off, int i) {
+    return (i < base_slots ? base : (char*)more.p) + off[i];
+  };
+  auto set_at = [&](char* q, bool with_v, PSet& s) {
+    for (int k = 0; k < 3; ++k) s.x[k] = q + pitch * k;
+    q += set_x;
+    if (with_v) {
+      for (int k = 0; k < 3; ++k) s.v[k] = q + pitch * k;
+      q += set_x;
+    }
+    s.lost = (uint8_t*)q;
+  };
+  std::vector<PSet> cks(kept < nck ? nck - kept + 1 : 0), xb(slots);
+  for (size_t i = 0; i < cks.size(); ++i) set_at(base + ck_off[i], true, cks[i]);
+  for (int i = 0; i < slots; ++i) set_at(slot_at(x_off, i), false, xb[i]);
   PSet& live = c->set[c->cur];
   // A record's fields are solved straight into it: each record has the
   // forward solves with their outputs there, and an instance whose fields
   // are there for the force pass and the reverse cycle to read.
-  InstDev<T>* const rinst = (InstDev<T>*)(base + in_off);
-  SolveDesc<T>* const rdesc = (SolveDesc<T>*)(base + sd_off);
+  char* const recs = more.p ? (char*)more.p : base;
+  InstDev<T>* const rinst = (InstDev<T>*)(recs + (more.p ? more_in : in_off));
+  SolveDesc<T>* const rdesc = (SolveDesc<T>*)(recs + (more.p ? more_sd : sd_off));
   std::vector<SolveDesc<T>> hdesc;
   std::vector<InstDev<T>> hinst(xb.size(), inst_of<T>(c));
   for (size_t r = 0; r < xb.size(); ++r) {
-    T* const f = (T*)(base + fb_off[r]);
+    T* const f = (T*)slot_at(f_off, (int)r);
     for (auto e : fwd.host) {
       e.phi = f + (e.phi - (T*)c->grid_block);
       hdesc.push_back(e);
