@@ -762,6 +762,7 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   for (size_t i = 0; i < cks.size(); ++i) set_at(base + ck_off[i], true, cks[i]);
   for (int i = 0; i < slots; ++i) set_at(slot_at(x_off, i), false, xb[i]);
   PSet& live = c->set[c->cur];
+  const bool copy = c->bound && c->cur == 1;  // live is the sorted copy
   // A record's fields are solved straight into it: each record has the
   // forward solves with their outputs there, and an instance whose fields
   // are there for the force pass and the reverse cycle to read.
@@ -808,9 +809,17 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
       SBX_TRY(force(c, 1));
     }
   }
-  if (kept < nck) SBX_TRY(copy_set<T>(c, cks.back(), live, true, true));  // final state
-  SBX_TRY(launch_adj_init<T>(dinst<T>(c), c->d_cur, n, sel_comp, sel_gal, lx, lv, gm, c->pre_partial,
-                             dloss, c->stream));
+  if (kept < nck && !copy) SBX_TRY(copy_set<T>(c, cks.back(), live, true, true));  // final state
+  // a sorted copy's final state goes home, where the loss is summed: its last
+  // bits do not depend on the order that the sort left within a cell
+  if (copy) {
+    const PartDev<T> home = pset_dev<T>(c->set[0], n);
+    SBX_TRY(launch_state_home<T>(pset_dev<T>(live, n), (T*)stage, home, c->stream));
+    SBX_TRY(launch_adj_init<T>(home, sel_comp, sel_gal, nullptr, nullptr, nullptr, c->pre_partial, dloss,
+                               c->stream));
+  }
+  SBX_TRY(launch_adj_init<T>(pset_dev<T>(live, n), sel_comp, sel_gal, lx, lv, gm, c->pre_partial,
+                             copy ? dloss + 1 : dloss, c->stream));
   const GridsDev<T> B = adj_grids<T>(c);
   SolvePlan<T>& adj = sizeof(T) == 8 ? (SolvePlan<T>&)c->adj64 : (SolvePlan<T>&)c->adj32;
   for (int seg = nck - 1; seg >= 0; --seg) {
@@ -835,9 +844,7 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
       SBX_TRY(launch_adj_gather<T>(dinst<T>(c), c->d_cur, n, at, B, gm, c->stream));
     }
   }
-  if (kept < nck) SBX_TRY(copy_set<T>(c, live, cks.back(), true, true));  // back to the final state
-  if (c->bound && c->cur == 1)
-    SBX_TRY(launch_state_home<T>(pset_dev<T>(live, n), (T*)stage, pset_dev<T>(c->set[0], n), c->stream));
+  if (kept < nck && !copy) SBX_TRY(copy_set<T>(c, live, cks.back(), true, true));  // back to the final state
   c->com_fresh = false;
   c->grids_fields = false;
   c->step_count += nsteps;

@@ -230,15 +230,15 @@ struct AdjCycle {
 };
 
 // Reverse mode of a leapfrog segment (single instance, fixed centres).
-// init: loss (one double) and seeds of the adjoints; step: one reverse cycle
+// init: loss (one double, summed in the order of p) and seeds of the adjoints
+// (lx null: the loss alone); step: one reverse cycle
 // at its positions and forward fields, adjoint sources scattered into B;
 // gather: mass gradient from the adjoint potentials P.  Particles that sat
 // out the cycle (lost at its start) pass their adjoints through unchanged
 // and gather nothing.
 template <typename T>
-sbx_status launch_adj_init(const InstDev<T>* inst, const int* cur, int64_t n, int sel_comp,
-                           int sel_gal, double* lx, double* lv, double* gm, double* partial,
-                           double* loss, hipStream_t s);
+sbx_status launch_adj_init(const PartDev<T>& p, int sel_comp, int sel_gal, double* lx, double* lv,
+                           double* gm, double* partial, double* loss, hipStream_t s);
 template <typename T>
 sbx_status launch_adj_step(const InstDev<T>* inst, int64_t n, const AdjCycle<T>& at,
                            const GridsDev<T>& B, double* lx, double* lv, hipStream_t s);

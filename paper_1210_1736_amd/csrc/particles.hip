@@ -1503,22 +1503,22 @@ __device__ __forceinline__ int adj_off(int k, int N) {
 
 // Seed: L = sum over the selected particles of 1/2 m vz^2; dL/dvz = m vz,
 // dL/dm = 1/2 vz^2 (explicit part); loss partial sums per block (fixed order).
+// lx null: the loss alone.
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_adj_init(const InstDev<T>* __restrict__ inst, const int* __restrict__ cur, int sel_comp,
-               int sel_gal, double* __restrict__ lx, double* __restrict__ lv,
+    k_adj_init(PartDev<T> p, int sel_comp, int sel_gal, double* __restrict__ lx, double* __restrict__ lv,
                double* __restrict__ gm, double* __restrict__ partial) {
-  const InstDev<T>& I = inst[0];
-  const PartDev<T> p = I.p[cur[0]];
   double acc = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    lx[3 * i] = lx[3 * i + 1] = lx[3 * i + 2] = 0.0;
-    lv[3 * i] = lv[3 * i + 1] = 0.0;
     const bool sel = p.comp[i] == sel_comp && p.gal[i] == sel_gal && !p.lost[i];
     const double m = (double)p.m[i], vz = (double)p.v[2][i];
-    lv[3 * i + 2] = sel ? m * vz : 0.0;
-    gm[i] = sel ? 0.5 * vz * vz : 0.0;
+    if (lx) {
+      lx[3 * i] = lx[3 * i + 1] = lx[3 * i + 2] = 0.0;
+      lv[3 * i] = lv[3 * i + 1] = 0.0;
+      lv[3 * i + 2] = sel ? m * vz : 0.0;
+      gm[i] = sel ? 0.5 * vz * vz : 0.0;
+    }
     if (sel) acc += 0.5 * m * vz * vz;
   }
   double v[1] = {acc};
@@ -1991,11 +1991,10 @@ sbx_status launch_indices(const InstDev<T>* inst, const int* cur, int64_t n, int
 
 
 template <typename T>
-sbx_status launch_adj_init(const InstDev<T>* inst, const int* cur, int64_t n, int sel_comp,
-                           int sel_gal, double* lx, double* lv, double* gm, double* partial,
-                           double* loss, hipStream_t s) {
-  hipLaunchKernelGGL((k_adj_init<T>), dim3(kRedBlocks), dim3(256), 0, s, inst, cur, sel_comp, sel_gal,
-                     lx, lv, gm, partial);
+sbx_status launch_adj_init(const PartDev<T>& p, int sel_comp, int sel_gal, double* lx, double* lv,
+                           double* gm, double* partial, double* loss, hipStream_t s) {
+  hipLaunchKernelGGL((k_adj_init<T>), dim3(kRedBlocks), dim3(256), 0, s, p, sel_comp, sel_gal, lx, lv, gm,
+                     partial);
   hipLaunchKernelGGL(k_reduce_one, dim3(1), dim3(256), 0, s, partial, kRedBlocks, loss);
   SBX_HIP(hipGetLastError());
   return SBX_OK;
@@ -2196,9 +2195,8 @@ sbx_status launch_grads_out(const int32_t* id, int64_t n, const double* gm, cons
                                      uint32_t*, size_t, uint32_t*, hipStream_t);                 \
   template sbx_status launch_indices<T>(const InstDev<T>*, const int*, int64_t, int, int,        \
                                         int32_t*, int8_t*, hipStream_t);                         \
-  template sbx_status launch_adj_init<T>(const InstDev<T>*, const int*, int64_t, int, int,       \
-                                         double*, double*, double*, double*, double*,            \
-                                         hipStream_t);                                           \
+  template sbx_status launch_adj_init<T>(const PartDev<T>&, int, int, double*, double*, double*, \
+                                         double*, double*, hipStream_t);                         \
   template sbx_status launch_adj_step<T>(const InstDev<T>*, int64_t, const AdjCycle<T>&,         \
                                          const GridsDev<T>&, double*, double*, hipStream_t);     \
   template sbx_status launch_adj_gather<T>(const InstDev<T>*, const int*, int64_t,               \
