@@ -1,6 +1,9 @@
 // C ABI of the library: contexts (particles, grids, forces, steps).  Host
 // code only orchestrates: every step of the method runs in the kernels of
 // fft.hip and particles.hip.
+#include <sys/mman.h>
+#include <unistd.h>
+
 #include "ctx.h"
 
 namespace sbx {
@@ -554,12 +557,15 @@ sbx_status ensure_acc(sbx_ctx* c) {
 
 // Take the page faults of a fresh output array while the GPU computes what
 // goes into it, not during the copy (a new 7 MB array of the caller's cost
-// about as much in faults as its transfer).
+// about as much in faults as its transfer).  The pages are populated with
+// their contents kept: an array whose call fails later is as it was.  Where
+// the kernel cannot (no such advice, or another kind of memory), the copy
+// takes the faults.
 void touch_pages(void* p, size_t bytes) {
-  if (!p) return;
-  volatile char* c = (volatile char*)p;
-  for (size_t i = 0; i < bytes; i += 4096) c[i] = 0;
-  if (bytes) c[bytes - 1] = 0;
+  if (!p || !bytes) return;
+  const uintptr_t page = (uintptr_t)sysconf(_SC_PAGESIZE);
+  const uintptr_t a = (uintptr_t)p & ~(page - 1), b = (uintptr_t)p + bytes;
+  (void)madvise((void*)a, b - a, MADV_POPULATE_WRITE);
 }
 
 sbx_status set_dt(sbx_ctx* c, double dt) {
