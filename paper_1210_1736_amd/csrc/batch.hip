@@ -115,7 +115,10 @@ sbx_status step_t(sbx_batch* b, int nsteps) {
       if (!b->exec[w]) SBX_TRY(capture<T>(b, w));
       SBX_HIP(hipGraphLaunch(b->exec[w], b->stream));
     }
-    if (with_sort) b->cur ^= 1;
+    if (with_sort) {
+      b->cur ^= 1;
+      b->sorted = true;
+    }
     ++b->step_count;
   }
   return SBX_OK;
@@ -143,6 +146,7 @@ void release(sbx_batch* b) {
 sbx_status write_back(sbx_batch* b) {
   for (sbx_ctx* c : b->ctx) {
     c->cur = b->cur;
+    c->ordered = c->ordered || b->sorted;
     c->com_fresh = b->fresh;
     c->solved = c->solved || b->step_count > 0;
     c->grids_fields = false;

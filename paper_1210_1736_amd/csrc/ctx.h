@@ -146,6 +146,7 @@ struct sbx_batch {
   int64_t step_count = 0;
   bool fresh = false;              // every instance's centre-of-mass sums are current
   bool pending = false;            // work queued since the last sbx_batch_sync
+  bool sorted = false;             // the particles have been put in cell order
   std::vector<double> dt;
 };
 
