@@ -24,7 +24,7 @@ struct Green {
 };
 
 // One set of particle arrays (device, context precision), carved from one
-// allocation of at least particle_block_bytes (null: borrowed storage).
+// allocation (alloc_set; null: borrowed storage).
 struct PSet {
   void* block = nullptr;
   void* x[3] = {};

@@ -1350,14 +1350,15 @@ __global__ void __launch_bounds__(NT)
 }
 
 // ------------------------------------------------------- small grids ---
-// N <= 16: the whole solve in one block and one launch.  The half spectrum,
-// (N+1) x 2N x N complex, stays in LDS at slot (kx, ky, z); rows y < N of a
-// (kx, z) line sit where its frequencies ky will.  A thread transforms a
-// line of 2N in registers (no twiddle tables, no exchanges); the five steps
-// are separated by block barriers.  The z lines, the most, get a thread each
-// (two rounds in FP64, whose 32 complex values need the registers).  What
-// bounds it is the chain of five steps: one 16^3 solve in FP32 took 18.4 us
-// as five launches, whose 18 us of kernels do next to no work.
+// N <= 16: the whole solve in one block and one launch (solves of one source,
+// see solves_disjoint).  The half spectrum, (N+1) x 2N x N complex, stays in
+// LDS at slot (kx, ky, z); rows y < N of a (kx, z) line sit where its
+// frequencies ky will.  A thread transforms a line of 2N in registers (no
+// twiddle tables, no exchanges); the five steps are separated by block
+// barriers.  The z lines, the most, get a thread each (two rounds in FP64,
+// whose 32 complex values need the registers).  What bounds it is the chain
+// of five steps: one 16^3 solve in FP32 took 18.4 us as five launches, whose
+// 18 us of kernels do next to no work.
 template <typename T, int N>
 struct SM {
   static constexpr int L = 2 * N, PZ = N + 1;
@@ -1383,14 +1384,6 @@ __global__ void __launch_bounds__(NT) k_small(const SolveDesc<T>* __restrict__ s
     C2<T> v[L];
 #pragma unroll
     for (int n = 0; n < N; ++n) v[n] = C2<T>{a[n], b[n]};
-    if (d.rho2) {  // summed grids: the second source is added on the way in
-      const gp<const T> a2 = glb(d.rho2 + ((size_t)z * N + 2 * j) * N), b2 = a2 + N;
-#pragma unroll
-      for (int n = 0; n < N; ++n) {
-        v[n].re += a2[n];
-        v[n].im += b2[n];
-      }
-    }
 #pragma unroll
     for (int n = N; n < L; ++n) v[n] = C2<T>{(T)0, (T)0};
     dftR<L, false>(v);
@@ -1844,7 +1837,7 @@ static bool small_form(int N, int count) { return N <= 16 && count <= kSmallCoun
 
 // In form 1 a solve writes its field while others still read their masses:
 // no solve may read what another one writes (the summed grids of a galaxy
-// do).
+// do, so k_small has no second source).
 template <typename T>
 static bool solves_disjoint(const SolveDesc<T>* d, int n) {
   for (int i = 0; i < n; ++i) {

@@ -2219,6 +2219,5 @@ template sbx_status launch_zero<uint8_t>(uint8_t*, size_t, hipStream_t);
 template sbx_status launch_unpermute<double>(const double*, const int32_t*, double*, int64_t, int, hipStream_t);
 template sbx_status launch_unpermute<int32_t>(const int32_t*, const int32_t*, int32_t*, int64_t, int, hipStream_t);
 template sbx_status launch_unpermute<int8_t>(const int8_t*, const int32_t*, int8_t*, int64_t, int, hipStream_t);
-template sbx_status launch_unpermute<uint8_t>(const uint8_t*, const int32_t*, uint8_t*, int64_t, int, hipStream_t);
 
 }  // namespace sbx
