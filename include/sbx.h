@@ -235,10 +235,11 @@ sbx_status sbx_diag_log(sbx_ctx* ctx, int32_t max, sbx_diag* out, int32_t* count
  * last ckpt_every cycles' positions and fields are kept from the forward; the
  * others are recomputed from (x, v) checkpoints every ckpt_every steps.  A
  * work buffer for these stays with the context until its particles or grids
- * are replaced.  While the call runs it may hold the records of earlier cycles
- * as well, instead of recomputing them, in up to 4 GiB and at most an eighth
- * of the device memory that is free then; they are given back before it
- * returns.  Loss L = sum over the live particles of component
+ * are replaced.  Where there is room the records of earlier cycles are held as
+ * well, instead of recomputing them: in up to 128 MiB (and a 256th of the
+ * device memory that is free) that stay with the work buffer, else in up to
+ * 4 GiB (and an eighth of it) that are given back before the call returns.
+ * Loss L = sum over the live particles of component
  * sel_comp of galaxy sel_gal of 1/2 m v_z^2, with v the staggered velocity
  * after the last kick.  Outputs (host, caller's particle order, any may be
  * NULL): loss (1), grad_m = dL/dm (n), grad_x = dL/dx (n*3) and

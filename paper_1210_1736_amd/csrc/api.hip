@@ -293,6 +293,8 @@ void free_particles(sbx_ctx* c) {
   free_typed(c->pot);
   free_ptr(c->adj_work);
   c->adj_work_bytes = 0;
+  free_ptr(c->adj_more);
+  c->adj_more_bytes = 0;
   free_ptr(c->an_work);
   c->an_work_bytes = 0;
   c->acc_n = 0;
@@ -310,6 +312,8 @@ void free_grids(sbx_ctx* c) {
   free_ptr(c->adj_block);
   free_ptr(c->adj_work);
   c->adj_work_bytes = 0;
+  free_ptr(c->adj_more);
+  c->adj_more_bytes = 0;
   free_ptr(c->grid_block);
   free_typed(c->fix);
   free_typed(c->count);
@@ -636,10 +640,15 @@ sbx_status ensure_sort_arrays(sbx_ctx* c) {
   return upload_inst(c);
 }
 
-// Records the forward of a segment may keep beyond its last interval, and the
-// part of the device's free memory it leaves alone.
+// Records the forward of a segment may keep beyond its last interval: up to
+// kKeepBytes and an eighth of the device's free memory while the call runs, of
+// which up to kStayBytes (and a 256th of the free memory) stay with the
+// context.  Freeing a buffer takes 0.1 ms for 8 MB and 0.4 for 64 MB and more,
+// whatever its size: a quarter of a five-cycle segment of three 64^3 levels in
+// FP64 with its 65 MB (1.84 ms, 2.33 with a buffer of the call's own), 4% of a
+// six-cycle one on 256^3 with 357 MB (8.49 and 8.87).
 constexpr size_t kKeepBytes = (size_t)4 << 30;
-constexpr size_t kKeepShare = 8;  // one eighth of it at most
+constexpr size_t kStayBytes = (size_t)128 << 20;
 
 // A device buffer of one call, given back when the call ends.
 struct CallBuffer {
@@ -655,11 +664,9 @@ struct CallBuffer {
 // Forward nsteps without sorting, then the reverse cycles interval by
 // interval.  The positions, lost flags and fields of the last interval's
 // cycles are kept from the forward pass, and those of the intervals before it
-// as far as kKeepBytes and an eighth of the free device memory hold them, in
-// a buffer of the call's own (allocating and freeing 4 GiB takes 0.3 ms each;
-// the solves it saves a six-cycle segment on a 256^3 grid, 12 instead of 16,
-// take 1.5); those of the others are recomputed from checkpoints of (x, v, lost)
-// every ckpt_every steps:
+// as far as kKeepBytes go (a six-cycle segment on a 256^3 grid then runs 12
+// solves instead of 16); those of the others are recomputed from checkpoints
+// of (x, v, lost) every ckpt_every steps:
 // each cycle's solve runs from the particles that take part in it (live
 // after its start-of-step loss test), and its lost flags and fields are kept
 // for the reverse cycle, which scatters the adjoint sources, solves them and
@@ -719,21 +726,22 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   double* stage = (double*)(base + st_off);
   if (sort) SBX_TRY(sort_particles(c, stage));  // runs while the host allocates below
   // intervals whose records the forward keeps: the last one, and the ones
-  // before it that the call's own buffer holds (records, and the descriptors
-  // and instance records of all)
+  // before it that a second buffer holds (records, and the descriptors and
+  // instance records of all)
   const size_t slot_bytes = set_x + n + gbytes + sizeof(SolveDesc<T>) * fwd.nsolves + sizeof(InstDev<T>) + 1024;
   int kept = 1;
-  CallBuffer more{c->stream};
+  size_t free_now = 0, total = 0;
   if (nck > 1) {
-    size_t free_now = 0, total = 0;
     if (hipMemGetInfo(&free_now, &total) != hipSuccess) {
       (void)hipGetLastError();
       free_now = 0;
     }
-    const size_t room = std::min(kKeepBytes, free_now / kKeepShare);
+    const size_t room = std::min(kKeepBytes, free_now / 8);
     kept = (int)std::min<size_t>(nck, 1 + room / (slot_bytes * ckpt));
   }
   int slots = (int)std::min<int64_t>((int64_t)kept * ckpt, nsteps);
+  char* more = nullptr;
+  CallBuffer own{c->stream};
   size_t more_sd = 0, more_in = 0;
   if (slots > base_slots) {
     need = 0;
@@ -745,7 +753,18 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     }
     more_sd = take(sizeof(SolveDesc<T>) * fwd.nsolves * slots);
     more_in = take(sizeof(InstDev<T>) * slots);
-    const sbx_status rc = dev_alloc(&more.p, need);
+    sbx_status rc = SBX_OK;
+    if (need <= c->adj_more_bytes) {
+      more = (char*)c->adj_more;
+    } else if (need <= std::min(kStayBytes, free_now / 256)) {
+      free_ptr(c->adj_more);
+      c->adj_more_bytes = 0;
+      if ((rc = dev_alloc(&c->adj_more, need)) == SBX_OK) c->adj_more_bytes = need;
+      more = (char*)c->adj_more;
+    } else {
+      rc = dev_alloc(&own.p, need);
+      more = (char*)own.p;
+    }
     if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
     if (rc != SBX_OK) {  // the last interval only
       kept = 1;
@@ -753,7 +772,7 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     }
   }
   auto slot_at = [&](const std::vector<size_t>& off, int i) {
-    return (i < base_slots ? base : (char*)more.p) + off[i];
+    return (i < base_slots ? base : more) + off[i];
   };
   auto set_at = [&](char* q, bool with_v, PSet& s) {
     for (int k = 0; k < 3; ++k) s.x[k] = q + pitch * k;
@@ -772,9 +791,8 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   // A record's fields are solved straight into it: each record has the
   // forward solves with their outputs there, and an instance whose fields
   // are there for the force pass and the reverse cycle to read.
-  char* const recs = more.p ? (char*)more.p : base;
-  InstDev<T>* const rinst = (InstDev<T>*)(recs + (more.p ? more_in : in_off));
-  SolveDesc<T>* const rdesc = (SolveDesc<T>*)(recs + (more.p ? more_sd : sd_off));
+  InstDev<T>* const rinst = (InstDev<T>*)(more ? more + more_in : base + in_off);
+  SolveDesc<T>* const rdesc = (SolveDesc<T>*)(more ? more + more_sd : base + sd_off);
   std::vector<SolveDesc<T>> hdesc;
   std::vector<InstDev<T>> hinst(xb.size(), inst_of<T>(c));
   for (size_t r = 0; r < xb.size(); ++r) {

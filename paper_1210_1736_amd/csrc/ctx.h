@@ -83,6 +83,8 @@ struct sbx_ctx {
   void* adj_block = nullptr;
   void* adj_work = nullptr;      // segment adjoint work arrays, kept between calls
   size_t adj_work_bytes = 0;
+  void* adj_more = nullptr;      // a few records beyond the last interval's (at most kStayBytes)
+  size_t adj_more_bytes = 0;
   void* an_work = nullptr;       // disc analysis work arrays, kept between calls
   size_t an_work_bytes = 0;
   sbx::SolvePlan<float> adj32;

@@ -48,3 +48,26 @@ def test_records_are_given_back(sbx, prec, ckpt):
         assert la == pytest.approx(lb, rel=1e-12 if f64 else 1e-6)
         for a, b, tol in zip(ga, gb, (1e-5, 1e-4, 1e-5)):
             assert _maxrel(a, b) < (1e-9 if f64 else 10 * tol)  # FP32: some cells differ after 40 cycles
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_few_records_stay_and_go_with_the_particles(sbx, prec):
+    """Up to 128 MiB of further records stay with the context, for segments
+    that need as many or fewer, until the particles are replaced."""
+    import torch
+    w = _workload("single", n=3000, seed=5)
+    ctx = sbx.Context(prec=prec, G=w.G)
+    ctx.sbx_build_grids([sbx.make_hierarchy([(64, w.hier[0].levels[0].R, 1.0)])])
+    ctx.sbx_load_particles(w.x, w.v, w.m, w.comp, w.gal)
+    ctx.sbx_adjoint_segment(1e-3, 1, 1, 1, 0)
+    time.sleep(0.2)
+    free, held = torch.cuda.mem_get_info()[0], []
+    for steps, every in ((20, 1), (20, 1), (7, 2), (20, 1)):
+        ctx.sbx_load_particles(w.x, w.v, w.m, w.comp, w.gal) if steps == 7 else None
+        ctx.sbx_adjoint_segment(1e-3, steps, every, 1, 0)
+        time.sleep(0.2)
+        held.append(free - torch.cuda.mem_get_info()[0])
+    record = 64 ** 3 * (8 if prec == sbx.SBX_FP64 else 4)
+    assert 15 * record < held[0] < 26 * record + (16 << 20)
+    assert held[1] == held[0] == held[3] and held[2] < held[0]
+    ctx.close()
