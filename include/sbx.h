@@ -235,10 +235,8 @@ sbx_status sbx_diag_log(sbx_ctx* ctx, int32_t max, sbx_diag* out, int32_t* count
  * last ckpt_every cycles' positions and fields are kept from the forward; the
  * others are recomputed from (x, v) checkpoints every ckpt_every steps.  A
  * work buffer for these stays with the context until its particles or grids
- * are replaced.  Where there is room the records of earlier cycles are held as
- * well, instead of recomputing them: in up to 128 MiB (and a 256th of the
- * device memory that is free) that stay with the work buffer, else in up to
- * 4 GiB (and an eighth of it) that are given back before the call returns.
+ * are replaced.  Records of earlier cycles are held beside it, instead of
+ * recomputing them, as far as sbx_set_segment_keep allows.
  * Loss L = sum over the live particles of component
  * sel_comp of galaxy sel_gal of 1/2 m v_z^2, with v the staggered velocity
  * after the last kick.  Outputs (host, caller's particle order, any may be
@@ -254,6 +252,15 @@ sbx_status sbx_diag_log(sbx_ctx* ctx, int32_t max, sbx_diag* out, int32_t* count
 sbx_status sbx_adjoint_segment(sbx_ctx* ctx, double dt, int32_t nsteps, int32_t ckpt_every,
                                int32_t sel_comp, int32_t sel_gal, double* loss, double* grad_m,
                                double* grad_x, double* grad_v);
+
+/* Most device memory (bytes >= 0, SBX_EINVAL otherwise) in which segments hold
+ * the records of cycles before the last ckpt_every ones; default 2^30, and
+ * never more than a 64th of the device memory that is free when a segment needs
+ * more of it.  A record is the grids and 3 n values and n bytes.  The buffer
+ * stays with the context until its particles or grids are replaced; a limit
+ * below its size gives it back at once, 0 leaves segments with what ckpt_every
+ * asks for.  A performance setting only. */
+sbx_status sbx_set_segment_keep(sbx_ctx* ctx, int64_t bytes);
 
 /* As sbx_adjoint_segment with grad_m, grad_x, grad_v in device memory of the
  * context's device (loss stays a host pointer). */

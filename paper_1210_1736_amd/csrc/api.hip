@@ -640,31 +640,17 @@ sbx_status ensure_sort_arrays(sbx_ctx* c) {
   return upload_inst(c);
 }
 
-// Records the forward of a segment may keep beyond its last interval: up to
-// kKeepBytes and an eighth of the device's free memory while the call runs, of
-// which up to kStayBytes (and a 256th of the free memory) stay with the
-// context.  Freeing a buffer takes 0.1 ms for 8 MB and 0.4 for 64 MB and more,
-// whatever its size: a quarter of a five-cycle segment of three 64^3 levels in
-// FP64 with its 65 MB (1.84 ms, 2.33 with a buffer of the call's own), 4% of a
-// six-cycle one on 256^3 with 357 MB (8.49 and 8.87).
-constexpr size_t kKeepBytes = (size_t)4 << 30;
-constexpr size_t kStayBytes = (size_t)128 << 20;
-
-// A device buffer of one call, given back when the call ends.
-struct CallBuffer {
-  hipStream_t s;
-  void* p = nullptr;
-  ~CallBuffer() {
-    if (!p) return;
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(p);
-  }
-};
+// The records a segment keeps beyond its last interval take this part of the
+// device's free memory at most (and keep_bytes).  They stay with the context:
+// a buffer of each call's own cost a six-cycle segment on a 256^3 grid (357 MB
+// of them) 0.4 ms of 8.5 in a small program, and 2.5 to 7 in one that had other
+// buffers and contexts before, most of it in hipFree.
+constexpr size_t kKeepShare = 64;
 
 // Forward nsteps without sorting, then the reverse cycles interval by
 // interval.  The positions, lost flags and fields of the last interval's
 // cycles are kept from the forward pass, and those of the intervals before it
-// as far as kKeepBytes go (a six-cycle segment on a 256^3 grid then runs 12
+// as far as keep_bytes go (a six-cycle segment on a 256^3 grid then runs 12
 // solves instead of 16); those of the others are recomputed from checkpoints
 // of (x, v, lost) every ckpt_every steps:
 // each cycle's solve runs from the particles that take part in it (live
@@ -730,18 +716,17 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
   // instance records of all)
   const size_t slot_bytes = set_x + n + gbytes + sizeof(SolveDesc<T>) * fwd.nsolves + sizeof(InstDev<T>) + 1024;
   int kept = 1;
-  size_t free_now = 0, total = 0;
-  if (nck > 1) {
+  if (nck > 1 && c->keep_bytes > 0) {
+    size_t free_now = 0, total = 0;
     if (hipMemGetInfo(&free_now, &total) != hipSuccess) {
       (void)hipGetLastError();
       free_now = 0;
     }
-    const size_t room = std::min(kKeepBytes, free_now / 8);
+    const size_t room = std::max(c->adj_more_bytes, std::min(c->keep_bytes, free_now / kKeepShare));
     kept = (int)std::min<size_t>(nck, 1 + room / (slot_bytes * ckpt));
   }
   int slots = (int)std::min<int64_t>((int64_t)kept * ckpt, nsteps);
   char* more = nullptr;
-  CallBuffer own{c->stream};
   size_t more_sd = 0, more_in = 0;
   if (slots > base_slots) {
     need = 0;
@@ -753,20 +738,15 @@ sbx_status adjoint_t(sbx_ctx* c, double dt, int nsteps, int ckpt, int sel_comp, 
     }
     more_sd = take(sizeof(SolveDesc<T>) * fwd.nsolves * slots);
     more_in = take(sizeof(InstDev<T>) * slots);
-    sbx_status rc = SBX_OK;
-    if (need <= c->adj_more_bytes) {
-      more = (char*)c->adj_more;
-    } else if (need <= std::min(kStayBytes, free_now / 256)) {
+    if (need > c->adj_more_bytes) {
       free_ptr(c->adj_more);
       c->adj_more_bytes = 0;
-      if ((rc = dev_alloc(&c->adj_more, need)) == SBX_OK) c->adj_more_bytes = need;
-      more = (char*)c->adj_more;
-    } else {
-      rc = dev_alloc(&own.p, need);
-      more = (char*)own.p;
+      const sbx_status rc = dev_alloc(&c->adj_more, need);
+      if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
+      if (rc == SBX_OK) c->adj_more_bytes = need;
     }
-    if (rc != SBX_OK && rc != SBX_ENOMEM) return rc;
-    if (rc != SBX_OK) {  // the last interval only
+    more = (char*)c->adj_more;
+    if (!more) {  // the last interval only
       kept = 1;
       slots = base_slots;
     }
@@ -1647,6 +1627,21 @@ sbx_status sbx_adjoint_segment_device(sbx_ctx* c, double dt, int32_t nsteps, int
                                       int32_t sel_comp, int32_t sel_gal, double* loss,
                                       double* grad_m, double* grad_x, double* grad_v) {
   return adjoint_impl(c, dt, nsteps, ckpt_every, sel_comp, sel_gal, loss, grad_m, grad_x, grad_v, true);
+}
+
+sbx_status sbx_set_segment_keep(sbx_ctx* c, int64_t bytes) {
+  if (!c || bytes < 0) {
+    set_error("bad argument");
+    return SBX_EINVAL;
+  }
+  SBX_TRY(set_device(c->cfg.device));
+  c->keep_bytes = (size_t)bytes;
+  if (c->adj_more_bytes > c->keep_bytes) {
+    SBX_HIP(hipStreamSynchronize(c->stream));  // no kernel in flight still uses them
+    free_ptr(c->adj_more);
+    c->adj_more_bytes = 0;
+  }
+  return SBX_OK;
 }
 
 sbx_status sbx_set_outer_merge(sbx_ctx* c, int32_t merge) {

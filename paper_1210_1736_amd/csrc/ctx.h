@@ -83,8 +83,9 @@ struct sbx_ctx {
   void* adj_block = nullptr;
   void* adj_work = nullptr;      // segment adjoint work arrays, kept between calls
   size_t adj_work_bytes = 0;
-  void* adj_more = nullptr;      // a few records beyond the last interval's (at most kStayBytes)
+  void* adj_more = nullptr;      // records beyond the last interval's, kept between calls
   size_t adj_more_bytes = 0;
+  size_t keep_bytes = (size_t)1 << 30;  // at most (sbx_set_segment_keep)
   void* an_work = nullptr;       // disc analysis work arrays, kept between calls
   size_t an_work_bytes = 0;
   sbx::SolvePlan<float> adj32;

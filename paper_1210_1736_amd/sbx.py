@@ -103,6 +103,7 @@ def _load():
         "sbx_set_sort_interval": (S, [P, I32]),
         "sbx_set_outer_merge": (S, [P, I32]),
         "sbx_set_deterministic_deposit": (S, [P, I32]),
+        "sbx_set_segment_keep": (S, [P, I64]),
         "sbx_adjoint_segment": (S, [P, D, I32, I32, I32, I32, P, P, P, P]),
         "sbx_adjoint_segment_device": (S, [P, D, I32, I32, I32, I32, P, P, P, P]),
         "sbx_load_particles_device": (S, [P, I64, P, P, P, P, P]),
@@ -341,6 +342,10 @@ class Context:
         _check(_lib.sbx_adjoint_segment(self._h, float(dt), int(nsteps), int(ckpt_every), int(sel_comp),
                                         int(sel_gal), _ptr(loss), _ptr(gm), _ptr(gx), _ptr(gv)))
         return float(loss[0]), gm, gx, gv
+
+    def sbx_set_segment_keep(self, nbytes):
+        """Limit of the device memory in which segments hold earlier cycles."""
+        _check(_lib.sbx_set_segment_keep(self._h, int(nbytes)))
 
     def sbx_set_outer_merge(self, merge):
         _check(_lib.sbx_set_outer_merge(self._h, int(merge)))
