@@ -345,8 +345,7 @@ def disc_analysis_rate(sbx, torch, w):
     ctx.close()
     return {"ms": 1e3 * (t1 - t0), "n_disc": out["n_disc"], "e_heat": out["e_heat"],
             "sig_z_over_sig_R": out["sig_z"] / out["sig_R"] if out["sig_R"] > 0 else None,
-            "includes": "selection, stable radix sort of the radii, bins, heat, annulus, "
-                        "allocations and host copies"}
+            "includes": "selection, radial order, bins, heat, annulus and host copies"}
 
 
 def cpu_threads():

@@ -658,8 +658,8 @@ constexpr size_t kKeepShare = 64;
 // for the reverse cycle, which scatters the adjoint sources, solves them and
 // gathers the mass gradient.  A particle lost during the segment thus
 // collects dL/dm from the cycles before its loss, and passes its adjoints
-// unchanged through the cycles it sat out.  Work arrays live in one device
-// buffer of the context, kept between calls.  Borrowed particles run as a
+// unchanged through the cycles it sat out.  Work arrays live in two device
+// buffers of the context, kept between calls.  Borrowed particles run as a
 // cell-sorted copy whose final state goes back to their storage: in the
 // order of a caller that does not sort, the scatter and the gathers of a
 // 2.05M-particle segment on a 256^3 grid took 1.30 ms (k_adj_step), 0.21
