@@ -168,7 +168,7 @@ sbx_status sbx_load_particles_device(sbx_ctx* ctx, int64_t n, const double* x, c
  * sbx_load: the caller keeps it alive and orders its own work on it with the
  * context stream.  Bound particles are never reordered: steps skip the cell
  * sort, a performance setting only, and a differentiable segment runs on a
- * sorted copy that the context keeps (43 or 71 bytes a particle in FP32 or
+ * sorted copy that the context keeps (43 or 72 bytes a particle in FP32 or
  * FP64, the sort's arrays included; without room for it the segment runs in
  * the caller's order).  A context holding them cannot join a batch.  Validated
  * on the device as sbx_load_particles_device (SBX_EINVAL); x, v and lost must
