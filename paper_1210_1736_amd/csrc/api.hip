@@ -643,8 +643,8 @@ sbx_status ensure_sort_arrays(sbx_ctx* c) {
 // The records a segment keeps beyond its last interval take this part of the
 // device's free memory at most (and keep_bytes).  They stay with the context:
 // a buffer of each call's own cost a six-cycle segment on a 256^3 grid (357 MB
-// of them) 0.4 ms of 8.5 in a small program, and 2.5 to 7 in one that had other
-// buffers and contexts before, most of it in hipFree.
+// of them) 0.4 ms of 8.5 in a small program, most of it in hipFree, and 2.5 to
+// 7 in one that had other buffers and contexts before.
 constexpr size_t kKeepShare = 64;
 
 // Forward nsteps without sorting, then the reverse cycles interval by
